@@ -1,201 +1,23 @@
 // GEMM kernels: C[M,N] = A[M,K] . B[N,K]^T with fused epilogues.
 //
-// bf16 path: LDS-tiled MFMA kernel (v_mfma_f32_16x16x32_bf16, wave64, 4 waves
-// per block), double-buffered LDS with register prefetch of the next K tile,
-// and an optional deterministic split-K: every K range writes its fp32
-// partial tile, the last block to arrive (device-scope ticket) sums the
-// partials in fixed range order and runs the epilogue.
+// bf16 path: few-row kernels that stream the weights, and for many rows a K that the
+// direct-to-LDS tiles (gemm_tile.h) do not take (not a multiple of 64) an LDS-tiled MFMA
+// kernel (v_mfma_f32_16x16x32_bf16, wave64, 4 waves per block), double-buffered LDS with
+// register prefetch of the next K tile, and an optional deterministic split-K: every K
+// range writes its fp32 partial tile, the last block to arrive (device-scope ticket)
+// sums the partials in fixed range order and runs the epilogue.
 //
 // fp32 path: a plain SIMT kernel (one output per thread) for the small fp32
 // models, which are latency bound.
 #include <algorithm>
 
-#include "kernels.h"
+#include "gemm_epilogue.h"
 
 namespace ravel {
-
-// Epilogues.  Every MFMA result fragment here holds 4 consecutive output columns
-// n .. n+3 of one row m per lane; epilogues are specialised by mode so that the
-// fully unrolled fragment loops stay small (a large inlined switch there makes
-// the compiler keep the accumulators in scratch memory).
-template <int MODE, typename T>
-RAVEL_DEV void epi1(const GemmArgs& a, int m, int n, float acc) {
-  const float b = a.bias ? a.bias[n] : 0.0f;
-  if constexpr (MODE == EPI_F32) {
-    a.out_f[(size_t)m * a.ldo_f + n] = acc + b;
-  } else if constexpr (MODE == EPI_T) {
-    ((T*)a.out_t)[(size_t)m * a.ldo_t + n] = act<T>::from_f(acc + b);
-  } else if constexpr (MODE == EPI_RESID) {
-    const size_t gm = a.gate_rows ? (size_t)a.gate_rows[m] : (size_t)m;
-    const float g = a.gate ? a.gate[gm * a.ldg + n] : 1.0f;
-    float* o = a.out_f + (size_t)m * a.ldo_f + n;
-    *o = *o + g * acc;
-  } else if constexpr (MODE == EPI_RESID_TANH) {
-    float* o = a.out_f + (size_t)m * a.ldo_f + n;
-    *o = *o + tanhf(*a.gate_scalar) * acc;
-  } else if constexpr (MODE == EPI_COND) {
-    const int blk = a.cond_grp ? a.cond_grp[m] : m;
-    if (blk < 0) return;
-    const float base = acc + b;
-    for (int i = 0; i < a.H; ++i)
-      ((T*)a.out_t)[((size_t)blk * a.H + i) * a.ldo_t + n] = act<T>::from_f(silu_f(a.ctau[(size_t)i * a.N + n] + base));
-  } else if constexpr (MODE == EPI_GELU_T) {
-    ((T*)a.out_t)[(size_t)m * a.ldo_t + n] = act<T>::from_f(gelu_tanh_f(acc + b));
-  } else if constexpr (MODE == EPI_SILU_T) {
-    ((T*)a.out_t)[(size_t)m * a.ldo_t + n] = act<T>::from_f(silu_f(acc + b));
-  }
-}
-
-// Whether the 4-column vector path applies to this launch (row strides aligned).
-RAVEL_DEV bool epi_vec_ok(const GemmArgs& a) {
-  switch (a.mode) {
-    case EPI_F32: return (a.ldo_f % 4) == 0;
-    case EPI_RESID: return (a.ldo_f % 4) == 0 && (!a.gate || (a.ldg % 4) == 0);
-    case EPI_RESID_TANH: return (a.ldo_f % 4) == 0;
-    case EPI_T:
-    case EPI_GELU_T:
-    case EPI_SILU_T: return (a.ldo_t % 4) == 0;
-    case EPI_COND: return (a.ldo_t % 4) == 0 && (a.N % 4) == 0;
-    default: return true;
-  }
-}
-
-RAVEL_DEV void store_bf16x4(bf16_t* p, float v0, float v1, float v2, float v3) {
-  u32x2_t w;
-  w[0] = (uint32_t)f32_to_bf16(v0) | ((uint32_t)f32_to_bf16(v1) << 16);
-  w[1] = (uint32_t)f32_to_bf16(v2) | ((uint32_t)f32_to_bf16(v3) << 16);
-  *(u32x2_t*)p = w;
-}
-
-// bf16 activations; fp32 outputs are written as float4.
-template <int MODE>
-RAVEL_DEV void epi4(const GemmArgs& a, int m, int n, f32x4_t v, bool vec) {
-  if (!(vec && n + 4 <= a.N)) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (n + r < a.N) epi1<MODE, bf16_t>(a, m, n + r, v[r]);
-    return;
-  }
-  f32x4_t b = {0.f, 0.f, 0.f, 0.f};
-  if (a.bias) b = *(const f32x4_t*)(a.bias + n);
-  if constexpr (MODE == EPI_F32) {
-    *(f32x4_t*)(a.out_f + (size_t)m * a.ldo_f + n) = f32x4_t{v[0] + b[0], v[1] + b[1], v[2] + b[2], v[3] + b[3]};
-  } else if constexpr (MODE == EPI_T) {
-    store_bf16x4((bf16_t*)a.out_t + (size_t)m * a.ldo_t + n, v[0] + b[0], v[1] + b[1], v[2] + b[2], v[3] + b[3]);
-  } else if constexpr (MODE == EPI_RESID || MODE == EPI_RESID_TANH) {
-    f32x4_t g = {1.f, 1.f, 1.f, 1.f};
-    if constexpr (MODE == EPI_RESID_TANH) {
-      const float t = tanhf(*a.gate_scalar);
-      g = f32x4_t{t, t, t, t};
-    } else {
-      if (a.gate) g = *(const f32x4_t*)(a.gate + (a.gate_rows ? (size_t)a.gate_rows[m] : (size_t)m) * a.ldg + n);
-    }
-    f32x4_t* o = (f32x4_t*)(a.out_f + (size_t)m * a.ldo_f + n);
-    f32x4_t x = *o;
-    x[0] = x[0] + g[0] * v[0];
-    x[1] = x[1] + g[1] * v[1];
-    x[2] = x[2] + g[2] * v[2];
-    x[3] = x[3] + g[3] * v[3];
-    *o = x;
-  } else if constexpr (MODE == EPI_COND) {
-    const int blk = a.cond_grp ? a.cond_grp[m] : m;
-    if (blk < 0) return;
-    // the time embeddings of 8 slots are loaded before any of their outputs is
-    // stored: one memory latency per 8 slots (the stores could alias the loads,
-    // so the compiler would otherwise wait for each load in turn)
-    for (int i0 = 0; i0 < a.H; i0 += 8) {
-      f32x4_t c[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        c[j] = (i0 + j < a.H) ? *(const f32x4_t*)(a.ctau + (size_t)(i0 + j) * a.N + n) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (i0 + j < a.H)
-          store_bf16x4((bf16_t*)a.out_t + ((size_t)blk * a.H + i0 + j) * a.ldo_t + n, silu_f(c[j][0] + v[0] + b[0]),
-                       silu_f(c[j][1] + v[1] + b[1]), silu_f(c[j][2] + v[2] + b[2]), silu_f(c[j][3] + v[3] + b[3]));
-    }
-  } else if constexpr (MODE == EPI_GELU_T) {
-    store_bf16x4((bf16_t*)a.out_t + (size_t)m * a.ldo_t + n, gelu_tanh_f(v[0] + b[0]), gelu_tanh_f(v[1] + b[1]),
-                 gelu_tanh_f(v[2] + b[2]), gelu_tanh_f(v[3] + b[3]));
-  } else if constexpr (MODE == EPI_SILU_T) {
-    store_bf16x4((bf16_t*)a.out_t + (size_t)m * a.ldo_t + n, silu_f(v[0] + b[0]), silu_f(v[1] + b[1]),
-                 silu_f(v[2] + b[2]), silu_f(v[3] + b[3]));
-  }
-}
-
-// Gated GeLU of a gate fragment g and its up fragment u: columns f .. f+3 of row m.
-RAVEL_DEV void epi_geglu4(const GemmArgs& a, int m, int f, f32x4_t g, f32x4_t u) {
-  store_bf16x4((bf16_t*)a.out_t + (size_t)m * a.ldo_t + f, gelu_tanh_f(g[0]) * u[0], gelu_tanh_f(g[1]) * u[1],
-               gelu_tanh_f(g[2]) * u[2], gelu_tanh_f(g[3]) * u[3]);
-}
-
-// Apply the epilogue to an NI x NJ grid of fragments: fragment (i, j) holds
-// rows m0 + 16 i + l16 and columns n0 + 16 j + 4 grp .. +3.
-template <int MODE, int NI, int NJ>
-RAVEL_DEV void epi_frags(const GemmArgs& a, const f32x4_t (&acc)[NI][NJ], int m0, int n0, int l16, int grp) {
-  const bool vec = epi_vec_ok(a);
-  if constexpr (MODE == EPI_GEGLU) {
-    if constexpr (NJ % 2 == 0) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; j += 2) {
-          const int m = m0 + i * 16 + l16;
-          const int ng = n0 + j * 16;  // gate block start (multiple of 32)
-          if (m < a.M && ng < a.N) epi_geglu4(a, m, (ng >> 5) * 16 + grp * 4, acc[i][j], acc[i][j + 1]);
-        }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int m = m0 + i * 16 + l16, n = n0 + j * 16 + grp * 4;
-        if (m < a.M && n < a.N) epi4<MODE>(a, m, n, acc[i][j], vec);
-      }
-  }
-}
-
-template <int NI, int NJ>
-RAVEL_DEV void epilogue(const GemmArgs& a, const f32x4_t (&acc)[NI][NJ], int m0, int n0, int l16, int grp) {
-  switch (a.mode) {
-    case EPI_F32: epi_frags<EPI_F32>(a, acc, m0, n0, l16, grp); break;
-    case EPI_T: epi_frags<EPI_T>(a, acc, m0, n0, l16, grp); break;
-    case EPI_RESID: epi_frags<EPI_RESID>(a, acc, m0, n0, l16, grp); break;
-    case EPI_RESID_TANH: epi_frags<EPI_RESID_TANH>(a, acc, m0, n0, l16, grp); break;
-    case EPI_GEGLU: epi_frags<EPI_GEGLU>(a, acc, m0, n0, l16, grp); break;
-    case EPI_COND: epi_frags<EPI_COND>(a, acc, m0, n0, l16, grp); break;
-    case EPI_GELU_T: epi_frags<EPI_GELU_T>(a, acc, m0, n0, l16, grp); break;
-    case EPI_SILU_T: epi_frags<EPI_SILU_T>(a, acc, m0, n0, l16, grp); break;
-    default: break;
-  }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------
-// Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD b % 8),
-// each with its own L2.  Give every XCD a contiguous range of row-major tiles so
-// that the tiles sharing an activation row panel share one L2.
-RAVEL_DEV int xcd_tile(int b, int T) {
-  const int x = b & 7, local = b >> 3;
-  const int q = T >> 3, r = T & 7;  // XCD x owns q + (x < r) tiles
-  const int start = x * q + (x < r ? x : r);
-  return start + local;
-}
-// Row and column of tile t of a tiles_m x tiles_n grid ordered in groups of up to 8
-// column tiles, row-major inside a group: an XCD's contiguous range of t covers a
-// compact rectangle (about 8 x 8 tiles), so its L2 holds the activation row panels and
-// the weight column panels it reads instead of every column panel of a wide output.
-RAVEL_DEV void tile_rc(int t, int tiles_m, int tiles_n, int& r, int& c) {
-  constexpr int GN = 8;
-  const int g = t / (tiles_m * GN);
-  const int gw = min(GN, tiles_n - g * GN);
-  const int ti = t - g * tiles_m * GN;
-  r = ti / gw;
-  c = g * GN + ti % gw;
-}
-
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs a) {
   constexpr int NT = 64 * WM * WN;  // threads per block
@@ -338,180 +160,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs a) {
   epilogue(a, acc, mw, nw, l16, grp);
 }
 
-
-// ---------------------------------------------------------------------------
-// Tiled GEMM, many rows, K tiles loaded straight into LDS (global_load_lds,
-// 16 bytes per lane): no register staging and no LDS store instructions.
-// STAGES LDS buffers; tile kt + STAGES - 1 is in flight while tile kt is
-// multiplied.  Rows are 64 bf16 (128 bytes, unpadded); the 16-byte chunk c of
-// row r sits at chunk position c ^ ((r >> 1) & 7), so the 16 rows read by one
-// fragment load hit 16 distinct bank groups.  Loads clamp rows to the matrix
-// (rows / columns past M / N only feed outputs that are never written); K and
-// the K range must be multiples of 64.  The fragment reads are inline asm with
-// an explicit LDS wait: as plain loads the compiler would wait for every
-// global->LDS load in flight (including later stages) before each of them, and
-// __syncthreads() would wait for them too, so the K loop uses s_barrier after
-// an explicit wait for this wave's loads of the current tile.
-// ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef const __attribute__((address_space(1))) void gmem_void_t;
-
-// gfx9 s_waitcnt immediate: vmcnt <= n, expcnt and lgkmcnt not waited for
-constexpr unsigned waitcnt_vm(int n) { return (unsigned)((n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8)); }
-
-// ROWLOOP: the row count is known on the device only (a.m_rows); block b owns
-// column tile b and runs every live row tile of it in turn (no K split, fp32
-// output: EPI_F32 only).
-// MODE: the epilogue, fixed at compile time (a run-time switch over the modes
-// makes the compiler keep the accumulators in scratch memory).
-template <int BM, int BN, int WM, int WN, int STAGES, int MODE, bool ROWLOOP = false>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_lds_kernel(GemmArgs a) {
-  constexpr int NW = WM * WN;
-  constexpr int BK = 64;
-  constexpr int TM = BM / (16 * WM), TN = BN / (16 * WN);
-  constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;  // 1 KB (8-row) segments per wave per tile
-  static_assert(LA >= 1 && LB >= 1 && (BM / 8) % NW == 0 && (BN / 8) % NW == 0, "segments per wave");
-  constexpr int AHEAD = STAGES - 1;
-  static_assert(AHEAD >= 1 && AHEAD <= 3, "stages");
-  __shared__ __attribute__((aligned(1024))) bf16_t As[STAGES][BM * BK];
-  __shared__ __attribute__((aligned(1024))) bf16_t Bs[STAGES][BN * BK];
-  __shared__ int s_last;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, grp = lane >> 4;
-  const int wm = wave / WN, wn = wave % WN;
-  const int tiles_n = (a.N + BN - 1) / BN;
-  int tile, m0, n0;
-  if constexpr (ROWLOOP) {
-    tile = blockIdx.x;
-    m0 = 0;
-    n0 = tile * BN;
-    a.M = min(a.M, *a.m_rows);
-  } else {
-    tile = xcd_tile(blockIdx.x, gridDim.x);
-    int tr, tc;
-    tile_rc(tile, gridDim.x / tiles_n, tiles_n, tr, tc);
-    m0 = tr * BM;
-    n0 = tc * BN;
-    if (a.m_rows) a.M = min(a.M, *a.m_rows);
-  }
-  if (m0 >= a.M) return;  // whole tile past a device-side row count (every K range alike)
-  const int z = blockIdx.z;
-  const int kbeg = z * a.kchunk;
-  const int kend = min(a.K, kbeg + a.kchunk);
-  const int nk = (kend - kbeg) / BK;
-  const bf16_t* __restrict__ A = (const bf16_t*)a.A;
-  const bf16_t* __restrict__ B = (const bf16_t*)a.B;
-
-  const int srow = lane >> 3, spos = lane & 7;  // lane -> (row in segment, chunk position)
-  auto issue = [&](int kt, int st) {
-    const int k0 = kbeg + kt * BK;
-#pragma unroll
-    for (int i = 0; i < LA; ++i) {
-      const int seg = wave * LA + i, row = seg * 8 + srow;
-      const int m = min(m0 + row, a.M - 1);
-      const int c = spos ^ ((row >> 1) & 7);
-      __builtin_amdgcn_global_load_lds((gmem_void_t*)(A + (size_t)m * a.lda + k0 + c * 8), (lds_void_t*)&As[st][seg * 512],
-                                       16, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < LB; ++i) {
-      const int seg = wave * LB + i, row = seg * 8 + srow;
-      const int n = min(n0 + row, a.N - 1);
-      const int c = spos ^ ((row >> 1) & 7);
-      __builtin_amdgcn_global_load_lds((gmem_void_t*)(B + (size_t)n * a.ldb + k0 + c * 8), (lds_void_t*)&Bs[st][seg * 512],
-                                       16, 0, 0);
-    }
-  };
-  auto frag = [&](const bf16_t* base, int row, int c) -> bf16x8_t {
-    const unsigned addr =
-        (unsigned)(size_t)(const __attribute__((address_space(3))) bf16_t*)(&base[row * BK + ((c ^ ((row >> 1) & 7)) * 8)]);
-    bf16x8_t v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
-    return v;
-  };
-
-  for (;;) {  // once, or (ROWLOOP) once per live row tile
-  f32x4_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < AHEAD; ++t)
-    if (t < nk) issue(t, t);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int st = kt % STAGES;
-    // this wave's loads of tile kt are complete once at most the later tiles'
-    // loads are outstanding (vector memory operations complete in order)
-    const int later = min(AHEAD - 1, nk - 1 - kt);
-    if (later >= 2)
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * (LA + LB)));
-    else if (later == 1)
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(LA + LB));
-    else
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __builtin_amdgcn_s_barrier();  // every wave's part of tile kt is in LDS; tile kt-1's buffer is free
-    if (kt + AHEAD < nk) issue(kt + AHEAD, (kt + AHEAD) % STAGES);
-    const bf16_t* as = As[st];
-    const bf16_t* bs = Bs[st];
-#pragma unroll
-    for (int ks = 0; ks < BK / 32; ++ks) {
-      bf16x8_t af[TM], bfr[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = frag(as, wm * (BM / WM) + i * 16 + l16, ks * 4 + grp);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bfr[j] = frag(bs, wn * (BN / WN) + j * 16 + l16, ks * 4 + grp);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-      for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(af[i]));
-#pragma unroll
-      for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(bfr[j]));
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-    }
-  }
-
-  const int mw = m0 + wm * (BM / WM);
-  const int nw = n0 + wn * (BN / WN);
-  if (a.ksplit > 1) {
-    const size_t tile_elems = (size_t)BM * BN;
-    float* part = a.partial + ((size_t)z * gridDim.x + tile) * tile_elems;
-    const int wbase = (wave * TM * TN) * 256;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) coherent_store4(part + wbase + ((i * TN + j) * 64 + lane) * 4, acc[i][j]);
-    if (!last_block_arrival(&a.counters[tile * kCounterStride], (unsigned)a.ksplit, &s_last)) return;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
-        for (int zz = 0; zz < a.ksplit; ++zz) {
-          const f32x4_t v = (zz == z) ? acc[i][j]
-                                      : *(const f32x4_t*)(a.partial + ((size_t)zz * gridDim.x + tile) * tile_elems + wbase +
-                                                          ((i * TN + j) * 64 + lane) * 4);
-          sum[0] += v[0];
-          sum[1] += v[1];
-          sum[2] += v[2];
-          sum[3] += v[3];
-        }
-        acc[i][j] = sum;
-      }
-  }
-  epi_frags<MODE>(a, acc, mw, nw, l16, grp);
-  if constexpr (!ROWLOOP) break;
-  m0 += BM;
-  if (m0 >= a.M) break;
-  // every wave's LDS reads of this tile completed before its MFMAs; the next
-  // tile's loads may overwrite the stages once all waves are here
-  __syncthreads();
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Weight-streaming kernel for few rows (M <= 64): the regime of one env's H
@@ -1053,62 +701,12 @@ static hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int MODE>
-static hipError_t launch_lds_tile_m(const GemmArgs& a, hipStream_t s) {
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  dim3 grid(tiles, 1, a.ksplit);
-  hipLaunchKernelGGL((gemm_lds_kernel<BM, BN, WM, WN, STAGES, MODE>), grid, dim3(64 * WM * WN), 0, s, a);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, int WM, int WN, int STAGES>
-static hipError_t launch_lds_tile(const GemmArgs& a, hipStream_t s) {
-  switch (a.mode) {
-    case EPI_F32: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_F32>(a, s);
-    case EPI_T: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_T>(a, s);
-    case EPI_RESID: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_RESID>(a, s);
-    case EPI_RESID_TANH: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_RESID_TANH>(a, s);
-    case EPI_GEGLU: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_GEGLU>(a, s);
-    case EPI_COND: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_COND>(a, s);
-    case EPI_GELU_T: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_GELU_T>(a, s);
-    case EPI_SILU_T: return launch_lds_tile_m<BM, BN, WM, WN, STAGES, EPI_SILU_T>(a, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// row-loop launches (device-side row count) have the fp32 epilogue only
-template <int BM, int BN, int WM, int WN, int STAGES>
-static hipError_t launch_lds_rows(const GemmArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_lds_kernel<BM, BN, WM, WN, STAGES, EPI_F32, true>), dim3((a.N + BN - 1) / BN),
-                     dim3(64 * WM * WN), 0, s, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_gemm_bf16(const GemmArgs& a, int tile, hipStream_t s) {
-  // direct-to-LDS variants (measured on MI355X at M = 3200: 128x128 with two
-  // stages 744-804 TF/s at K = 1024; 128x64 with three stages 514-581 TF/s at
-  // N = 1024, K = 2048-4096) where K tiles are whole and rows 16-byte aligned
-  const bool lds_ok = a.K % 64 == 0 && a.kchunk % 64 == 0 && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
-                      ((uintptr_t)a.A % 16) == 0 && ((uintptr_t)a.B % 16) == 0 && a.M > 0 && a.N > 0;
-  // device-side row count (few distinct rows, many columns): 256-row tiles, one
-  // block per column tile, so every weight byte is streamed once
-  if (lds_ok && a.m_rows && a.ksplit == 1 && a.mode == EPI_F32) return launch_lds_rows<256, 128, 4, 2, 2>(a, s);
-  if (lds_ok && tile == TILE_128x128) return launch_lds_tile<128, 128, 2, 2, 2>(a, s);
-  if (lds_ok && tile == TILE_128x64) return launch_lds_tile<128, 64, 2, 2, 3>(a, s);
-  // larger wave tiles (64x128 .. 128x128) read less LDS per MFMA flop
-  if (lds_ok && tile == TILE_128x256) return launch_lds_tile<128, 256, 2, 2, 2>(a, s);
-  if (lds_ok && tile == TILE_256x128) return launch_lds_tile<256, 128, 2, 2, 2>(a, s);
-  if (lds_ok && tile == TILE_256x256) return launch_lds_tile<256, 256, 2, 2, 2>(a, s);
   switch (tile) {
     case TILE_128x128: return launch_tile<128, 128, 2, 2>(a, s);
-    case TILE_64x128: return launch_tile<64, 128, 2, 2>(a, s);
     case TILE_128x64: return launch_tile<128, 64, 2, 2>(a, s);
-    case TILE_32x64: return launch_tile<32, 64, 1, 4>(a, s);
-    case TILE_256x128: return launch_tile<256, 128, 2, 2>(a, s);
-    case TILE_128x256: return launch_tile<128, 256, 2, 2>(a, s);
-    case TILE_256x256: return launch_tile<256, 256, 4, 2>(a, s);
-    case TILE_64x64:
-    default: return launch_tile<64, 64, 2, 2>(a, s);
+    case TILE_64x128:
+    default: return launch_tile<64, 128, 2, 2>(a, s);
   }
 }
 

@@ -29,6 +29,8 @@ enum EpiMode {
   EPI_COND = 5,       // out_t[m*H+i, n] = T(silu(ctau[i,n] + acc + bias[n])) for i < H
   EPI_GELU_T = 6,     // out_t[m,n]  = T(gelu_tanh(acc + bias[n]))
   EPI_SILU_T = 7,     // out_t[m,n]  = T(silu(acc + bias[n]))
+  EPI_PART = 8,       // partial[z][m][n] = the sum over K range z (row-major, N a multiple of 4), summed by
+                      // launch_resid_norm
 };
 
 struct GemmArgs {
@@ -61,11 +63,20 @@ struct GemmArgs {
   int nrm_w;
 };
 
-// Tile configurations of the bf16 MFMA GEMM.
-enum GemmTile {
-  TILE_64x64 = 0, TILE_128x128 = 1, TILE_64x128 = 2, TILE_128x64 = 3, TILE_32x64 = 4,
-  TILE_256x128 = 5, TILE_128x256 = 6, TILE_256x256 = 7
+// bf16 GEMM with K tiles loaded straight into LDS (gemm_tile.h): K a multiple of 64,
+// 16-byte aligned rows.  K is split for EPI_PART only, which needs ksplit * M * N floats
+// at a.partial.  With a.m_rows: EPI_F32 over the device's row count.
+struct TilePlan {
+  int tile, bm, bn;
+  int ksplit, kchunk;
+  int items;  // row tiles x column tiles x K ranges
 };
+bool tile_ok(const GemmArgs& a);
+TilePlan plan_tile(int M, int N, int K, int mode);
+hipError_t launch_gemm_tile(GemmArgs a, const TilePlan& p, hipStream_t s);
+
+// Tile configurations of the register-staged bf16 MFMA GEMM.
+enum GemmTile { TILE_128x128 = 1, TILE_64x128 = 2, TILE_128x64 = 3 };
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, int tile, hipStream_t s);
 // M <= 64 weight-streaming kernel: block columns 64*nfr (nfr 1 or 2, 2 for EPI_GEGLU),
@@ -119,6 +130,17 @@ template <typename T>
 hipError_t launch_adarms(const float* x, int ldx, int M, int w, const float* scale,
                          const float* shift, int ldm, int mode, const int* rowmap, float eps, T* y, int ldy,
                          hipStream_t s);
+// The residual update after a split-K GEMM, and the norm after it, in one pass over x:
+//   x[m,:] += gate * sum_z part[z][m][:], gate row g(m) of `gate` (stride ldm), or
+//             tanh(*gate_scalar) with gate = NULL;
+//   y[m,:]  = bf16(adaptive norm of the new x): mode and operands as for launch_adarms
+//             (y = NULL: no norm).
+// With rowmap, g(m) and the scale / shift row are rowmap[m]; x and part rows of w floats,
+// w a multiple of 4, at most kResidNormMaxW.
+constexpr int kResidNormMaxW = 4096;
+hipError_t launch_resid_norm(const float* part, int ksplit, float* x, int M, int w, const float* gate,
+                             const float* gate_scalar, const float* scale, const float* shift, int ldm, int mode,
+                             const int* rowmap, float eps, bf16_t* y, hipStream_t s);
 // Groups of envs whose offset conditioning is identical within a step (equal
 // observation time t_obs, hence equal context age and delta): group g is the
 // g-th distinct t_obs in env order.  grp[e] = g for the first env of its group

@@ -88,7 +88,7 @@ struct LayerW {
   void* qkv_w = nullptr;
   void* o_w = nullptr;
   void* gu_w = nullptr;  // [2F, w], gate/up interleaved in blocks of 16 rows
-  void* down_w = nullptr;
+  void* down_w = nullptr;  // [w, Fp]
   int adapter = -1;  // index into the adapter list, -1 = none
   float* gamma = nullptr;
   void* qa_w = nullptr;
@@ -98,6 +98,7 @@ struct LayerW {
 
 struct ravel_model {
   ravel_config cfg;
+  int Fp = 0;  // row length of the MLP's hidden rows and of down_w (bf16: mlp_dim padded with zeros to whole K tiles of 64)
   bool bf16 = true;
   size_t elt = 2;
   int device = 0;
@@ -430,7 +431,7 @@ namespace {
 
 template <typename T>
 ravel_status run_gemm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const char* name, const void* A,
-                      int lda, const void* W, int ldb, int M, int N, int K, GemmArgs epi) {
+                      int lda, const void* W, int ldb, int M, int N, int K, GemmArgs epi, bool layer = false) {
   ravel_model* m = b->m;
   epi.A = A;
   epi.lda = lda;
@@ -443,6 +444,7 @@ ravel_status run_gemm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const
   double obytes = (double)M * N * (epi.mode == EPI_F32 ? 4 : elt);
   if (epi.mode == EPI_RESID) obytes = (double)M * N * 12;  // read x, gate; write x
   if (epi.mode == EPI_RESID_TANH) obytes = (double)M * N * 8;
+  if (epi.mode == EPI_PART) obytes = (double)M * N * 4;
   if (epi.mode == EPI_GEGLU) obytes = (double)M * (N / 2) * elt;
   if (epi.mode == EPI_COND) obytes = (double)M * m->cfg.horizon * N * elt;
   const double bytes = ((double)M * K + (double)N * K) * elt + obytes;
@@ -456,16 +458,34 @@ ravel_status run_gemm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const
     return RAVEL_OK;
   }
   if ((K % 8) || (lda % 8) || (ldb % 8)) return fail(RAVEL_E_SHAPE, std::string(name) + ": K and strides must be multiples of 8");
+  epi.partial = b->gpart;
+  // direct-to-LDS tiles for many rows, and for the layers' GEMMs at any row count (the
+  // few-row kernels stay for the others: at most 64 rows and no chain of partial sums)
+  if ((M > 64 || layer || epi.mode == EPI_PART) && tile_ok(epi)) {
+    const TilePlan t = plan_tile(M, N, K, epi.mode);
+    if (epi.mode == EPI_PART && (size_t)t.ksplit * M * N > b->gpart_elems)
+      return fail(RAVEL_E_STATE, std::string(name) + ": GEMM workspace too small");
+    if (rec) {
+      char full[48];
+      if (epi.m_rows)  // rows known on the device only: no byte / flop figures
+        snprintf(full, sizeof full, "gemm_rows:%s", name);
+      else
+        snprintf(full, sizeof full, "gemm%dx%d:%s", t.bm, t.bn, name);
+      rec->begin(full, epi.m_rows ? 0.0 : bytes, epi.m_rows ? 0.0 : flops);
+    }
+    HIP_TRY(launch_gemm_tile(epi, t, s));
+    if (rec) rec->end();
+    return RAVEL_OK;
+  }
   const GemmPlan p = plan_gemm(M, N, K, epi.mode == EPI_GEGLU);
   epi.ksplit = epi.m_rows ? 1 : p.ksplit;  // device row count: whole K per block
   epi.kchunk = epi.m_rows ? K : p.kchunk;
-  epi.partial = b->gpart;
   epi.counters = b->gcnt;
   if (p.part_elems > b->gpart_elems || p.tiles > b->gcnt_n)
     return fail(RAVEL_E_STATE, std::string(name) + ": GEMM workspace too small");
   if (epi.m_rows && p.skinny) return fail(RAVEL_E_STATE, std::string(name) + ": device row count needs a tiled GEMM");
   if (rec) {
-    static const char* tn[] = {"64x64", "128x128", "64x128", "128x64", "32x64", "256x128", "128x256", "256x256"};
+    static const char* tn[] = {"", "128x128", "64x128", "128x64"};
     char full[48];
     if (epi.m_rows)  // rows known on the device only: no byte / flop figures
       snprintf(full, sizeof full, "gemm_rows:%s", name);
@@ -592,6 +612,59 @@ ravel_status enqueue_offset_adapter(ravel_buffer* b, hipStream_t s, KernelRecord
   return RAVEL_OK;
 }
 
+// The norm that follows a residual update: rows of scale and shift (stride ldm), or a
+// per-feature scale (mode 1); scale = NULL: none.
+struct NormOf {
+  const float* scale;
+  const float* shift;
+  int mode;
+};
+
+// x += gate * (A W^T), then y = norm(x).  bf16 models: the GEMM leaves the sums of its K
+// ranges and one kernel adds them, updates x and normalises; otherwise a residual
+// epilogue and the norm kernel.
+template <typename T>
+ravel_status resid_norm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const char* name, const void* A, int lda,
+                        const void* W, int ldb, int K, const float* gate, const float* gate_scalar, int ldm,
+                        const int* rowmap, const NormOf& nm) {
+  const ravel_config& c = b->m->cfg;
+  const int BH = b->B * c.horizon, w = c.width;
+  const double elt = (double)b->m->elt;
+  if constexpr (sizeof(T) == 2) {
+    GemmArgs e = epi_args(EPI_PART);
+    e.A = A;
+    e.lda = lda;
+    e.B = W;
+    e.ldb = ldb;
+    e.M = BH;
+    e.N = w;
+    e.K = K;
+    if (tile_ok(e) && w <= kResidNormMaxW) {
+      RV_TRY(run_gemm<T>(b, s, rec, name, A, lda, W, ldb, BH, w, K, e));
+      const int ks = plan_tile(BH, w, K, EPI_PART).ksplit;
+      REC_BEGIN("resid_norm", (double)BH * w * (4.0 * ks + 20 + elt), (double)BH * w * (ks + 7));
+      HIP_TRY(launch_resid_norm(b->gpart, ks, b->x, BH, w, gate, gate_scalar, nm.scale, nm.shift, ldm, nm.mode, rowmap,
+                                c.rms_eps, nm.scale ? (bf16_t*)b->y : nullptr, s));
+      REC_END();
+      return RAVEL_OK;
+    }
+  }
+  GemmArgs e = epi_args(gate ? EPI_RESID : EPI_RESID_TANH);
+  e.out_f = b->x;
+  e.ldo_f = w;
+  e.gate = gate;
+  e.ldg = ldm;
+  e.gate_rows = gate ? rowmap : nullptr;
+  e.gate_scalar = gate_scalar;
+  RV_TRY(run_gemm<T>(b, s, rec, name, A, lda, W, ldb, BH, w, K, e));
+  if (!nm.scale) return RAVEL_OK;
+  REC_BEGIN("adarms", (double)BH * w * (12 + elt), (double)BH * w * 5);
+  HIP_TRY(launch_adarms<T>(b->x, w, BH, w, nm.scale, nm.shift, ldm, nm.mode, nm.mode == 0 ? rowmap : nullptr, c.rms_eps,
+                           (T*)b->y, w, s));
+  REC_END();
+  return RAVEL_OK;
+}
+
 template <typename T>
 ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s, KernelRecorder* rec,
                                  const PassIn& pin) {
@@ -666,24 +739,37 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
     e.m_rows = b->cgroups ? b->crows : nullptr;
     RV_TRY(run_gemm<T>(b, s, rec, "mod_all", b->cond, w, m->mod_all_w, w, BH, ldm, w, e));
   }
+  // the norm before layer l's attention; layer c.layers: the final norm (mod_all)
+  const auto norm1 = [&](int l) {
+    const float* md = b->mod + (size_t)l * 6 * w;
+    return NormOf{md, md + w, 0};
+  };
+  const auto adarms = [&](const NormOf& nm, int ld) -> ravel_status {
+    REC_BEGIN("adarms", (double)BH * w * (12 + elt), (double)BH * w * 5);
+    HIP_TRY(launch_adarms<T>(b->x, w, BH, w, nm.scale, nm.shift, ld, nm.mode, nm.mode == 0 ? rowmap : nullptr,
+                             c.rms_eps, (T*)b->y, w, s));
+    REC_END();
+    return RAVEL_OK;
+  };
+  if (b->mod_all) RV_TRY(adarms(norm1(0), ldm));
   for (int l = 0; l < c.layers; ++l) {
     const LayerW& L = m->layers[l];
     const float* mod = b->mod_all ? b->mod + (size_t)l * 6 * w : b->mod;
+    const NormOf norm2{mod + 3 * w, mod + 4 * w, 0};
+    const bool ad = L.adapter >= 0 && fop;
     if (!b->mod_all) {
       GemmArgs e = epi_args(EPI_F32);
       e.bias = L.mod_b;
       e.out_f = b->mod;
       e.ldo_f = ldm;
       RV_TRY(run_gemm<T>(b, s, rec, "mod", b->cond, w, L.mod_w, w, BH, 6 * w, w, e));
+      RV_TRY(adarms(NormOf{mod, mod + w, 0}, ldm));
     }
-    REC_BEGIN("adarms", (double)BH * w * (12 + elt), (double)BH * w * 5);
-    HIP_TRY(launch_adarms<T>(b->x, w, BH, w, mod, mod + w, ldm, 0, rowmap, c.rms_eps, (T*)b->y, w, s));
-    REC_END();
     {
       GemmArgs e = epi_args(EPI_T);
       e.out_t = b->qkv;
       e.ldo_t = qkvd;
-      RV_TRY(run_gemm<T>(b, s, rec, "qkv", b->y, w, L.qkv_w, w, BH, qkvd, w, e));
+      RV_TRY(run_gemm<T>(b, s, rec, "qkv", b->y, w, L.qkv_w, w, BH, qkvd, w, e, true));
     }
     if (m->rope_cs) {
       REC_BEGIN("rope", (double)BH * (qd + kvd) * 2 * elt + (double)H * c.head_dim * 4, 0.0);
@@ -711,24 +797,14 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
       a.ldo = qd;
       RV_TRY(run_attn<T>(b, s, rec, "attn", a));
     }
-    {
-      GemmArgs e = epi_args(EPI_RESID);
-      e.out_f = b->x;
-      e.ldo_f = w;
-      e.gate = mod + 2 * w;
-      e.ldg = ldm;
-      e.gate_rows = rowmap;
-      RV_TRY(run_gemm<T>(b, s, rec, "o", b->att, qd, L.o_w, qd, BH, w, qd, e));
-    }
-    if (L.adapter >= 0 && fop) {
-      REC_BEGIN("adarms", (double)BH * w * (8 + elt), (double)BH * w * 4);
-      HIP_TRY(launch_adarms<T>(b->x, w, BH, w, L.gamma, nullptr, 0, 1, nullptr, c.rms_eps, (T*)b->y, w, s));
-      REC_END();
+    RV_TRY(resid_norm<T>(b, s, rec, "o", b->att, qd, L.o_w, qd, qd, mod + 2 * w, nullptr, ldm, rowmap,
+                         ad ? NormOf{L.gamma, nullptr, 1} : norm2));
+    if (ad) {
       {
         GemmArgs e = epi_args(EPI_T);
         e.out_t = b->qa;
         e.ldo_t = qd;
-        RV_TRY(run_gemm<T>(b, s, rec, "fop_q", b->y, w, L.qa_w, w, BH, qd, w, e));
+        RV_TRY(run_gemm<T>(b, s, rec, "fop_q", b->y, w, L.qa_w, w, BH, qd, w, e, true));
       }
       {
         AttnArgs a;
@@ -752,46 +828,27 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
         a.ldo = qd;
         RV_TRY(run_attn<T>(b, s, rec, "fop_attn", a));
       }
-      {
-        GemmArgs e = epi_args(EPI_RESID_TANH);
-        e.out_f = b->x;
-        e.ldo_f = w;
-        e.gate_scalar = L.alpha;
-        RV_TRY(run_gemm<T>(b, s, rec, "fop_o", b->att, qd, L.oa_w, qd, BH, w, qd, e));
-      }
+      RV_TRY(resid_norm<T>(b, s, rec, "fop_o", b->att, qd, L.oa_w, qd, qd, nullptr, L.alpha, ldm, rowmap, norm2));
     }
-    REC_BEGIN("adarms", (double)BH * w * (12 + elt), (double)BH * w * 5);
-    HIP_TRY(launch_adarms<T>(b->x, w, BH, w, mod + 3 * w, mod + 4 * w, ldm, 0, rowmap, c.rms_eps, (T*)b->y, w, s));
-    REC_END();
     {
       GemmArgs e = epi_args(EPI_GEGLU);
       e.out_t = b->u;
-      e.ldo_t = F;
-      RV_TRY(run_gemm<T>(b, s, rec, "gate_up", b->y, w, L.gu_w, w, BH, 2 * F, w, e));
+      e.ldo_t = m->Fp;
+      RV_TRY(run_gemm<T>(b, s, rec, "gate_up", b->y, w, L.gu_w, w, BH, 2 * F, w, e, true));
     }
-    {
-      GemmArgs e = epi_args(EPI_RESID);
-      e.out_f = b->x;
-      e.ldo_f = w;
-      e.gate = mod + 5 * w;
-      e.ldg = ldm;
-      e.gate_rows = rowmap;
-      RV_TRY(run_gemm<T>(b, s, rec, "down", b->u, F, L.down_w, F, BH, w, F, e));
-    }
+    // without mod_all the next layer's modulation is not there yet
+    RV_TRY(resid_norm<T>(b, s, rec, "down", b->u, m->Fp, L.down_w, m->Fp, m->Fp, mod + 5 * w, nullptr, ldm, rowmap,
+                         b->mod_all ? norm1(l + 1) : NormOf{nullptr, nullptr, 0}));
   }
   // final adaptive norm and output head
-  const float* fmod = b->mod_all ? b->mod + (size_t)c.layers * 6 * w : b->fmod;
-  const int ldf = b->mod_all ? ldm : 2 * w;
   if (!b->mod_all) {
     GemmArgs e = epi_args(EPI_F32);
     e.bias = m->fmod_b;
     e.out_f = b->fmod;
     e.ldo_f = 2 * w;
     RV_TRY(run_gemm<T>(b, s, rec, "final_mod", b->cond, w, m->fmod_w, w, BH, 2 * w, w, e));
+    RV_TRY(adarms(NormOf{b->fmod, b->fmod + w, 0}, 2 * w));
   }
-  REC_BEGIN("adarms", (double)BH * w * (12 + elt), (double)BH * w * 5);
-  HIP_TRY(launch_adarms<T>(b->x, w, BH, w, fmod, fmod + w, ldf, 0, rowmap, c.rms_eps, (T*)b->y, w, s));
-  REC_END();
   {
     GemmArgs e = epi_args(EPI_F32);
     e.bias = m->out_b;
@@ -1199,6 +1256,7 @@ ravel_status build_persistent(ravel_buffer* b) {
     }
     {
       Phase ph = gemm(u, F, nullptr, false, L.down_w, w, F, PE_RESID);
+      ph.g.ldw = m->Fp;
       ph.g.a_t32 = 1;
       ph.g.a_coh = u_pieces ? 1 : 0;
       resid(ph, mod + 5 * w, nullptr, NS_ROW, next_scale);
@@ -1685,6 +1743,8 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
     for (int l = 0; l < L; ++l)
       if (l % stride == stride - 1) ad_of[l] = n_ad++;
   m->n_ad = n_ad;
+  const int Fp = m->bf16 ? (F + 63) / 64 * 64 : F;
+  m->Fp = Fp;
   m->layers.resize(L);
 
   // shape checks
@@ -1767,7 +1827,7 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
     ar.want(&Lw.qkv_w, (size_t)qkvd * w * E);
     ar.want(&Lw.o_w, (size_t)w * qd * E);
     ar.want(&Lw.gu_w, (size_t)2 * F * w * E);
-    ar.want(&Lw.down_w, (size_t)w * F * E);
+    ar.want(&Lw.down_w, (size_t)w * Fp * E);
     Lw.adapter = ad_of[l];
     if (ad_of[l] >= 0) {
       ar.want((void**)&Lw.gamma, (size_t)w * 4);
@@ -1827,6 +1887,19 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
   do {                                                        \
     if ((st = up(name, dst, md)) != RAVEL_OK) return bail(done(st)); \
   } while (0)
+  // [w, k] rows placed in [w, kp] with zero padding (model dtype)
+  auto up_padded = [&](const char* name, void* dst, int k, int kp) -> ravel_status {
+    const size_t src_row = (size_t)k * E, dst_row = (size_t)kp * E;
+    void* tmp = nullptr;
+    if (hipMalloc(&tmp, (size_t)w * src_row) != hipSuccess) return fail(RAVEL_E_NOMEM, std::string(name) + " staging");
+    ravel_status s2 = up(name, tmp, true);
+    if (s2 == RAVEL_OK &&
+        (hipMemset(dst, 0, (size_t)w * dst_row) != hipSuccess ||
+         hipMemcpy2D(dst, dst_row, tmp, src_row, src_row, w, hipMemcpyDeviceToDevice) != hipSuccess))
+      s2 = fail(RAVEL_E_HIP, std::string(name) + " upload");
+    (void)hipFree(tmp);
+    return s2;
+  };
   UP("in.w", m->in_w, false);
   if (launch_transpose_f32(m->in_w, w, Din, m->in_wT, 0) != hipSuccess)
     return bail(done(fail(RAVEL_E_HIP, "in.w transpose")));
@@ -1844,17 +1917,8 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
       return bail(done(fail(RAVEL_E_HIP, "rope table")));
   }
   if (oadapter) {
-    // action-time MLP, first layer: [w, 2w + 1] rows placed in [w, at_kz] with zero padding
-    const size_t src_row = (size_t)(2 * w + 1) * E, dst_row = (size_t)m->at_kz * E;
-    void* tmp = nullptr;
-    if (hipMalloc(&tmp, (size_t)w * src_row) != hipSuccess) return bail(done(fail(RAVEL_E_NOMEM, "at.w1 staging")));
-    st = up("at.w1", tmp, true);
-    if (st == RAVEL_OK && (hipMemset(m->at_w1, 0, (size_t)w * dst_row) != hipSuccess ||
-                           hipMemcpy2D(m->at_w1, dst_row, tmp, src_row, src_row, w, hipMemcpyDeviceToDevice) !=
-                               hipSuccess))
-      st = fail(RAVEL_E_HIP, "at.w1 upload");
-    (void)hipFree(tmp);
-    if (st != RAVEL_OK) return bail(done(st));
+    // action-time MLP, first layer: [w, 2w + 1] rows placed in [w, at_kz]
+    if ((st = up_padded("at.w1", m->at_w1, 2 * w + 1, m->at_kz)) != RAVEL_OK) return bail(done(st));
     UP("at.b1", m->at_b1, false);
     UP("at.w2", m->at_w2, true);
     UP("at.b2", m->at_b2, false);
@@ -1876,7 +1940,11 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
     UP((p + "mod.b").c_str(), Lw.mod_b, false);
     UP((p + "qkv.w").c_str(), Lw.qkv_w, true);
     UP((p + "o.w").c_str(), Lw.o_w, true);
-    UP((p + "down.w").c_str(), Lw.down_w, true);
+    if (Fp == F) {
+      UP((p + "down.w").c_str(), Lw.down_w, true);
+    } else if ((st = up_padded((p + "down.w").c_str(), Lw.down_w, F, Fp)) != RAVEL_OK) {
+      return bail(done(st));
+    }
     // gate/up interleave: dst row 32b + j <- gate row 16b + j, dst row 32b + 16 + j <- up row 16b + j
     {
       const ravel_tensor* g = tm.get(p + "gate.w");
@@ -1991,11 +2059,10 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
       ar.want(&b->tz, (size_t)BH * m->at_kz * E);
       ar.want(&b->th, (size_t)BH * w * E);
     }
-    // few rows: every layer's modulation comes from one GEMM at the start of the step
-    // Few rows, or rows grouped by offset conditioning: every layer's modulation
+    // Few rows, one env (at most 128 rows), or rows grouped by offset conditioning: every layer's modulation
     // comes from one GEMM at the start of the step (on the groups' rows only).
     b->cgroups = BH > 64 && B > 1 && B <= kCondGroupsMaxB;
-    b->mod_all = BH <= 64 || b->cgroups;
+    b->mod_all = BH <= 64 || b->cgroups || B == 1;
     b->mod_ld = b->mod_all ? (6 * c.layers + 2) * w : 6 * w;
     if (b->cgroups) {
       ar.want((void**)&b->cgrp, (size_t)B * 4);
@@ -2008,7 +2075,7 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     ar.want(&b->att, (size_t)BH * qd * E);
     ar.want(&b->qa, (size_t)BH * qd * E);
     if (m->n_ad > 0) ar.want(&b->kva, (size_t)B * c.n_fop * m->n_ad * 2 * kvd * E);
-    ar.want(&b->u, (size_t)BH * F * E);
+    ar.want(&b->u, (size_t)BH * m->Fp * E);  // columns F .. Fp stay zero
     ar.want((void**)&b->fmod, (size_t)BH * 2 * w * 4);
     ar.want(&b->fhid, (size_t)B * w * E);
     ar.want(&b->obs_t, (size_t)B * std::max(c.fop_obs_dim, 1) * E);
@@ -2031,6 +2098,10 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
       part_elems = std::max(part_elems, p.part_elems);
       cnt = std::max(cnt, (size_t)p.tiles);
     }
+    // the residual GEMMs' partial sums
+    if (m->bf16)
+      for (int K : {qd, m->Fp})
+        if (K % 64 == 0) part_elems = std::max(part_elems, (size_t)plan_tile(BH, w, K, EPI_PART).ksplit * BH * w);
     // attention key split: aim for ~256 blocks when B * nq is small, >= 64 keys per split
     const int nkeys = c.prefix_len + H;
     const int blocks = B * c.n_q_heads;
