@@ -9,8 +9,6 @@
 // O^T += V^T P^T directly, without an LDS round trip.  With several key
 // splits, each block writes (m, l, unnormalised O) and the last block of the
 // (env, head) merges the splits in fixed order.
-//
-// fp32 path: one wavefront per (query, head, env), lanes over head dims.
 #include "kernels.h"
 
 namespace ravel {
@@ -591,65 +589,6 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s) {
     case 256: return two ? launch_hd<256, 2>(a, s) : launch_hd<256, 1>(a, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-// ---------------------------------------------------------------------------
-// fp32 path
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
-  const int query = blockIdx.x, j = blockIdx.y, e = blockIdx.z;
-  const int lane = threadIdx.x;
-  const int hd = a.hd;
-  const int g = (j * a.nkv) / a.nq;
-  const int slot = a.slot ? a.slot[e] : 0;
-  const float* pk = (const float*)a.pk + slot * a.p_slot_stride + e * a.p_env_stride;
-  const float* pv = (const float*)a.pv + slot * a.p_slot_stride + e * a.p_env_stride;
-  const float* sk = (const float*)a.sk;
-  const float* sv = (const float*)a.sv;
-  const float* q = (const float*)a.q + (size_t)(e * a.Hq + query) * a.ldq + j * hd;
-  float qv[4], ov[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int d = lane + 64 * c;
-    qv[c] = d < hd ? q[d] : 0.f;
-    ov[c] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int nkeys = a.P + a.S;
-  for (int kidx = 0; kidx < nkeys; ++kidx) {
-    const float* kr = key_base(a, pk, sk, e, kidx, g, hd);
-    const float* vr = key_base(a, pv, sv, e, kidx, g, hd);
-    float part = 0.f;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int d = lane + 64 * c;
-      if (d < hd) part += qv[c] * kr[d];
-    }
-    const float sc = wave_sum(part) * a.scale;
-    const float mnew = fmaxf(m, sc);
-    const float corr = expf(m - mnew);
-    const float p = expf(sc - mnew);
-    l = l * corr + p;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int d = lane + 64 * c;
-      ov[c] = ov[c] * corr + (d < hd ? p * vr[d] : 0.f);
-    }
-    m = mnew;
-  }
-  float* out = (float*)a.out + (size_t)(e * a.Hq + query) * a.ldo + j * hd;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int d = lane + 64 * c;
-    if (d < hd) out[d] = ov[c] / l;
-  }
-}
-
-hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s) {
-  if (a.hd > 256) return hipErrorInvalidValue;
-  dim3 grid(a.Hq, a.nq, a.B);
-  hipLaunchKernelGGL(attn_f32_kernel, grid, dim3(64), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace ravel

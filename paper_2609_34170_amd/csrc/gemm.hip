@@ -6,9 +6,6 @@
 // register prefetch of the next K tile, and an optional deterministic split-K: every K
 // range writes its fp32 partial tile, the last block to arrive (device-scope ticket)
 // sums the partials in fixed range order and runs the epilogue.
-//
-// fp32 path: a plain SIMT kernel (one output per thread) for the small fp32
-// models, which are latency bound.
 #include <algorithm>
 
 #include "gemm_epilogue.h"
@@ -708,53 +705,6 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int tile, hipStream_t s) {
     case TILE_64x128:
     default: return launch_tile<64, 128, 2, 2>(a, s);
   }
-}
-
-// ---------------------------------------------------------------------------
-// fp32 SIMT kernel
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  const int n = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int m = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (a.m_rows) a.M = min(a.M, *a.m_rows);
-  if (m >= a.M) return;
-  const float* __restrict__ A = (const float*)a.A + (size_t)m * a.lda;
-  const float* __restrict__ B = (const float*)a.B;
-  if (a.mode == EPI_GEGLU) {
-    const int F = a.N / 2;
-    if (n >= F) return;
-    const int rg = (n >> 4) * 32 + (n & 15);
-    const float* bg = B + (size_t)rg * a.ldb;
-    const float* bu = B + (size_t)(rg + 16) * a.ldb;
-    float g = 0.f, u = 0.f;
-    for (int k = 0; k < a.K; ++k) {
-      g += A[k] * bg[k];
-      u += A[k] * bu[k];
-    }
-    ((float*)a.out_t)[(size_t)m * a.ldo_t + n] = gelu_tanh_f(g) * u;
-  } else {
-    if (n >= a.N) return;
-    const float* b = B + (size_t)n * a.ldb;
-    float acc = 0.f;
-    for (int k = 0; k < a.K; ++k) acc += A[k] * b[k];
-    switch (a.mode) {
-      case EPI_F32: epi1<EPI_F32, float>(a, m, n, acc); break;
-      case EPI_T: epi1<EPI_T, float>(a, m, n, acc); break;
-      case EPI_RESID: epi1<EPI_RESID, float>(a, m, n, acc); break;
-      case EPI_RESID_TANH: epi1<EPI_RESID_TANH, float>(a, m, n, acc); break;
-      case EPI_COND: epi1<EPI_COND, float>(a, m, n, acc); break;
-      case EPI_GELU_T: epi1<EPI_GELU_T, float>(a, m, n, acc); break;
-      case EPI_SILU_T: epi1<EPI_SILU_T, float>(a, m, n, acc); break;
-      default: break;
-    }
-  }
-}
-
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-  const int ncols = a.mode == EPI_GEGLU ? a.N / 2 : a.N;
-  dim3 grid((ncols + 63) / 64, (a.M + 3) / 4);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace ravel
