@@ -110,13 +110,16 @@ struct AttnArgs {
   float scale;
   void* out; int ldo;              // out[(e*Hq + i)*ldo + j*hd + d]
   int nsplit, keys_per_split;      // split of the key range (multiple of 32)
-  float* part_o;                   // [B*nq*nsplit][Hq_pad][hd] (persistent kernel: fp16, normalised)
-  float* part_ml;                  // [B*nq*nsplit][Hq_pad][2]
-  unsigned* counters;              // [B*nq]
+  float* part_o;                   // [nsplit][B*Hq][nq*hd], unnormalised (persistent kernel: fp16
+                                   // [B*nq*nsplit][Hq_pad][hd], normalised)
+  float* part_ml;                  // [nsplit][B*Hq][nq][2] (persistent kernel: [B*nq*nsplit][Hq_pad][2])
+  unsigned* counters;              // persistent kernel: [B*nq]
   int coop;                        // persistent kernel: the splits of a head merge together
   int coh;                         // persistent kernel: device-coherent loads of q and the self rows
 };
 
+// Chooses nsplit and keys_per_split from the shape; with nsplit > 1 the launch needs part_o and part_ml.
+void plan_attn(AttnArgs& a);
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 

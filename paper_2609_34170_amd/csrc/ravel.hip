@@ -366,9 +366,7 @@ struct ravel_buffer {
   int gcnt_n = 0;
   float* apart_o = nullptr;
   float* apart_ml = nullptr;
-  unsigned* acnt = nullptr;
   int* dbg_flag = nullptr;
-  int attn_nsplit = 1, attn_kps = 0;
   bool mod_all = false;
   int mod_ld = 0;
   // persistent step: the modulation of layers 1 .. L - 1 and of the final norm (and
@@ -532,16 +530,10 @@ ravel_status run_attn(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const
   a.hd = c.head_dim;
   a.scale = 1.0f / sqrtf((float)c.head_dim);
   const int nkeys = a.P + a.S;
-  if (m->bf16 && a.S > 0 && b->attn_nsplit > 1) {
-    a.nsplit = b->attn_nsplit;
-    a.keys_per_split = b->attn_kps;
-  } else {
-    a.nsplit = 1;
-    a.keys_per_split = ((nkeys + 31) / 32) * 32;
-  }
+  a.nsplit = 1;
+  if (m->bf16 && a.S > 0) plan_attn(a);
   a.part_o = b->apart_o;
   a.part_ml = b->apart_ml;
-  a.counters = b->acnt;
   const double elt = (double)m->elt;
   const double bytes = (double)b->B * (a.Hq * (double)c.n_q_heads * c.head_dim * 2 * elt +
                                        (double)nkeys * c.n_kv_heads * c.head_dim * 2 * elt);
@@ -2102,27 +2094,20 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     if (m->bf16)
       for (int K : {qd, m->Fp})
         if (K % 64 == 0) part_elems = std::max(part_elems, (size_t)plan_tile(BH, w, K, EPI_PART).ksplit * BH * w);
-    // attention key split: aim for ~256 blocks when B * nq is small, >= 64 keys per split
-    const int nkeys = c.prefix_len + H;
-    const int blocks = B * c.n_q_heads;
-    int ns = 1;
-    if (m->bf16 && blocks < 64) {
-      // a few blocks per CU-group at batch 1: split keys, >= 128 keys per split; the
-      // merge keeps nsplit x H softmax weights in the 32-key tile's LDS
-      ns = std::min((nkeys + 127) / 128, (64 + blocks - 1) / blocks);
-      const int cap = 32 * (c.head_dim + 8) / 2 / H;
-      ns = std::max(1, std::min(ns, cap));
+    // partial outputs of the self-attention's key ranges
+    AttnArgs at;
+    memset(&at, 0, sizeof at);
+    at.B = B;
+    at.Hq = at.S = H;
+    at.P = c.prefix_len;
+    at.nq = c.n_q_heads;
+    at.nkv = c.n_kv_heads;
+    at.hd = c.head_dim;
+    if (m->bf16) plan_attn(at);
+    if (at.nsplit > 1) {
+      ar.want((void**)&b->apart_o, (size_t)at.nsplit * BH * qd * 4);
+      ar.want((void**)&b->apart_ml, (size_t)at.nsplit * BH * c.n_q_heads * 2 * 4);
     }
-    int kps = ((nkeys + ns - 1) / ns + 31) / 32 * 32;
-    ns = (nkeys + kps - 1) / kps;
-    b->attn_nsplit = ns;
-    b->attn_kps = kps;
-    if (ns > 1) {
-      const int Hp = (H + 15) / 16 * 16;
-      ar.want((void**)&b->apart_o, (size_t)blocks * ns * Hp * c.head_dim * 4);
-      ar.want((void**)&b->apart_ml, (size_t)blocks * ns * Hp * 2 * 4);
-    }
-    ar.want((void**)&b->acnt, (size_t)blocks * 4 * kCounterStride);
   }
   ar.want((void**)&b->gpart, std::max<size_t>(part_elems, 1) * 4);
   ar.want((void**)&b->gcnt, cnt * 4 * kCounterStride);
