@@ -161,7 +161,7 @@ int64_t ravel_model_weight_bytes(const ravel_model* model);
  * (seed lo, seed hi) with counter (j/4, env, r lo, r hi) and Box-Muller in
  * float64 rounded to float32.  Synchronous.
  * Environment variables read here (each "1" to apply), for tests and comparisons:
- *   RAVEL_NO_PERSISTENT   the per-kernel path even where the persistent kernel fits;
+ *   RAVEL_NO_PERSISTENT   the per-kernel path even where the persistent kernel is the default;
  *   RAVEL_NO_FUSED_XATTN  a separate attention phase for the FOP adapters in the
  *                         persistent kernel (default for one env with 256-dim heads
  *                         and <= 16 FOP tokens: computed inside the output projection);
@@ -192,12 +192,12 @@ void ravel_buffer_destroy(ravel_buffer* buf);
  *                           execution path; one graph per pointer set); 0: launch
  *                           the step's kernels eagerly.
  *   RAVEL_OPT_DEBUG         1: synchronise and check for NaN/Inf after each kernel.
- *   RAVEL_OPT_PERSISTENT    1 (default where available): run the transformer layers
- *                           of a bf16 model whose B*H rows fit one 64-row tile as a
- *                           single persistent kernel (one block per CU, grid
- *                           barriers between phases) between the few kernels around
- *                           it; 0: one kernel per operation.  E_STATE if the buffer
- *                           does not qualify.
+ *   RAVEL_OPT_PERSISTENT    1 (available for a bf16 model whose B*H rows fit one 64-row
+ *                           tile; the default up to 3 layers of width 512): run the
+ *                           transformer layers as a single persistent kernel (one
+ *                           block per CU, grid barriers between phases) between the
+ *                           few kernels around it; 0: one kernel per operation.
+ *                           E_STATE if the buffer does not qualify.
  *   RAVEL_OPT_FAIL_LAYERS   test hook, 1: mark the persistent layers' kernel as failed
  *                           (synchronises, then sets its error word as a grid barrier
  *                           that timed out would; every later launch then returns at

@@ -481,17 +481,22 @@ __global__ __launch_bounds__(256) void offset_cond_kernel(const int64_t* t, cons
                                                           const bf16_t* __restrict__ wd2,
                                                           const float* __restrict__ bd2, int w,
                                                           const float* __restrict__ ctau, int tau_row,
-                                                          bf16_t* __restrict__ cond) {
-  offset_cond_block(blockIdx.x, blockIdx.y, t, t_obs, ages, H, delta_bias, wd1, bd1, wd2, bd2, w, ctau, tau_row, cond);
+                                                          const int* __restrict__ grp, bf16_t* __restrict__ cond) {
+  const int e = blockIdx.y, blk = grp ? grp[e] : e;
+  if (blk < 0) return;  // not the first env of its group
+  offset_cond_block(blockIdx.x, e, t, t_obs, ages, H, delta_bias, wd1, bd1, wd2, bd2, w, ctau, tau_row,
+                    cond + ((size_t)blk - e) * H * w);
 }
+
+bool offset_cond_ok(int w, int H) { return w <= kCondMaxW && w % 8 == 0 && H <= kCondMaxH; }
 
 hipError_t launch_offset_cond(const int64_t* t, const int64_t* t_obs, const int64_t* ages, int B, int H,
                               float delta_bias, const float* wd1, const float* bd1, const bf16_t* wd2,
-                              const float* bd2, int w, const float* ctau, int tau_row, bf16_t* cond,
+                              const float* bd2, int w, const float* ctau, int tau_row, const int* grp, bf16_t* cond,
                               hipStream_t s) {
-  if (w > kCondMaxW || w % 8 || B < 1 || H > kCondMaxH) return hipErrorInvalidValue;
+  if (!offset_cond_ok(w, H) || B < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(offset_cond_kernel, dim3((w + kCondCols - 1) / kCondCols, B), dim3(256), 0, s, t, t_obs, ages, H,
-                     delta_bias, wd1, bd1, wd2, bd2, w, ctau, tau_row, cond);
+                     delta_bias, wd1, bd1, wd2, bd2, w, ctau, tau_row, grp, cond);
   return hipGetLastError();
 }
 
@@ -635,7 +640,7 @@ hipError_t launch_offset_cond_in_proj(const int64_t* t, const int64_t* t_obs, in
                                       const float* wd1, const float* bd1, const bf16_t* wd2, const float* bd2, int w,
                                       const float* ctau, bf16_t* cond, const float* X, int D, const float* w_inT,
                                       const float* b_in, float* x, float* sumsq, hipStream_t s) {
-  if (w > kCondMaxW || w % 64 || B < 1 || H > kCondMaxH || B * H > 64 || !t || !sumsq) return hipErrorInvalidValue;
+  if (w > kCondMaxW || w % 64 || B < 1 || H > kCondMaxH || B * H > 64 || !t) return hipErrorInvalidValue;
   InProjNorm nrm{};
   nrm.sumsq = sumsq;
   const int ncx = (w + kCondCols - 1) / kCondCols, nc = ncx * B;

@@ -200,15 +200,17 @@ struct InProjNorm {
 // The offset conditioning of a few envs in one launch (bf16 models): delta_e as for
 // launch_delta_hidden, h1 = bf16(silu(wd1 delta_e + bd1)), d = wd2 h1 + bd2 (wd2 bf16
 // [w, w]), cond[e*H + i, n] = bf16(silu(ctau[r, n] + d[n])) with r as for
-// launch_cond_expand.  w <= 2048, a multiple of 8; H <= 128.
+// launch_cond_expand; with grp as for launch_cond_expand too.  offset_cond_ok: w <= 2048, a
+// multiple of 8; H <= 128.
+bool offset_cond_ok(int w, int H);
 hipError_t launch_offset_cond(const int64_t* t, const int64_t* t_obs, const int64_t* ages, int B, int H,
                               float delta_bias, const float* wd1, const float* bd1, const bf16_t* wd2,
-                              const float* bd2, int w, const float* ctau, int tau_row, bf16_t* cond,
+                              const float* bd2, int w, const float* ctau, int tau_row, const int* grp, bf16_t* cond,
                               hipStream_t s);
 // launch_offset_cond (rolling step: ages and tau_row unused) and launch_in_proj (ring
 // in slot order from the step counter t, no offset input) in one launch, the input
-// projection writing x and the rows' per-64-column sums of squares (sumsq[tile][64])
-// only: the first norm's p and shift copies then come from the modulation GEMM
+// projection writing x and, with sumsq, the rows' per-64-column sums of squares
+// (sumsq[tile][64]) only: the first norm's p and shift copies then come from the modulation GEMM
 // (GemmArgs nrm_*).  B * H <= 64, w a multiple of 64.
 hipError_t launch_offset_cond_in_proj(const int64_t* t, const int64_t* t_obs, int B, int H, float delta_bias,
                                       const float* wd1, const float* bd1, const bf16_t* wd2, const float* bd2, int w,

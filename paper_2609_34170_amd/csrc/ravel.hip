@@ -676,42 +676,62 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   const bool concat = c.offset_mode == RAVEL_OFFSET_CONCAT;
   const bool no_mlp = c.offset_mode != RAVEL_OFFSET_MLP;
   const float dbias = pin.lead_bias ? c.delta_bias : 0.f;
-  if (no_mlp) {
-    REC_BEGIN("offset_value", (double)B * 12, 0.0);
-    HIP_TRY(launch_offset_value(pin.X ? nullptr : b->t, b->t_obs, pin.ages, B, H, dbias, b->dval, s));
-    REC_END();
-  } else {
-    REC_BEGIN("delta_hidden", (double)B * w * (8 + elt), (double)B * w * 4);
-    HIP_TRY(launch_delta_hidden<T>(pin.X ? nullptr : b->t, b->t_obs, pin.ages, B, H, dbias, m->d_w1, m->d_b1, w,
-                                   (T*)b->h1, s));
-    REC_END();
-  }
+  const float* ctau = pin.ctau ? pin.ctau : m->ctau;
+  const int64_t* tstep = pin.X ? nullptr : b->t;
   // Envs with equal t_obs have equal delta, so equal cond rows and modulation
   // rows: cond is written once per group (compacted) and the modulation GEMM
   // runs on the groups' rows only.
   const int* rowmap = b->cgroups ? b->crowmap : nullptr;
+  const int* grp = b->cgroups ? b->cgrp : nullptr;
   if (b->cgroups) {
     REC_BEGIN("cond_groups", (double)B * 8 + (double)BH * 4, 0.0);
     // equal context ages give equal offsets (the shared t makes equal t_obs equal ages)
     HIP_TRY(launch_cond_groups(pin.ages ? pin.ages : b->t_obs, B, H, b->cgrp, b->crowmap, b->crows, s));
     REC_END();
   }
-  if (!no_mlp) {
-    GemmArgs e = epi_args(EPI_F32);
-    e.bias = m->d_b2;
-    e.out_f = b->dvec;
-    e.ldo_f = w;
-    RV_TRY(run_gemm<T>(b, s, rec, "cond", b->h1, w, m->d_w2, w, B, w, w, e));
+  // A few envs: the offset MLP, its embedding and the conditioning rows in one launch (each
+  // env's blocks read W_d2 again, which the L2s hold: 6 us against 4 + 8 + 5 at one env of
+  // width 1024), on a rolling step of at most 64 rows with the input projection too.
+  const bool few = sizeof(T) == 2 && !no_mlp && B <= 16 && offset_cond_ok(w, H);
+  const bool with_in = few && !b->cgroups && !pin.X && !pin.ages && !pin.ctau && pin.tau_row < 0 && BH <= 64 && w % 64 == 0;
+  if (with_in) {
+    REC_BEGIN("offset_cond_in_proj", (double)w * w * elt + (double)H * w * 4 + (double)BH * w * elt + (double)BH * (D + w) * 4,
+              2.0 * B * w * w + (double)BH * w * 4 + 2.0 * BH * w * D);
+    HIP_TRY(launch_offset_cond_in_proj(b->t, b->t_obs, B, H, dbias, m->d_w1, m->d_b1, (const bf16_t*)m->d_w2, m->d_b2,
+                                       w, m->ctau, (bf16_t*)b->cond, b->X, D, m->in_wT, m->in_b, b->x, nullptr, s));
+    REC_END();
+  } else if (few) {
+    REC_BEGIN("offset_cond", (double)w * w * elt + (double)H * w * 4 + (double)BH * w * elt,
+              2.0 * B * w * w + (double)BH * w * 4);
+    HIP_TRY(launch_offset_cond(tstep, b->t_obs, pin.ages, B, H, dbias, m->d_w1, m->d_b1, (const bf16_t*)m->d_w2,
+                               m->d_b2, w, ctau, pin.tau_row, grp, (bf16_t*)b->cond, s));
+    REC_END();
+  } else {
+    if (no_mlp) {
+      REC_BEGIN("offset_value", (double)B * 12, 0.0);
+      HIP_TRY(launch_offset_value(tstep, b->t_obs, pin.ages, B, H, dbias, b->dval, s));
+      REC_END();
+    } else {
+      REC_BEGIN("delta_hidden", (double)B * w * (8 + elt), (double)B * w * 4);
+      HIP_TRY(launch_delta_hidden<T>(tstep, b->t_obs, pin.ages, B, H, dbias, m->d_w1, m->d_b1, w, (T*)b->h1, s));
+      REC_END();
+      GemmArgs e = epi_args(EPI_F32);
+      e.bias = m->d_b2;
+      e.out_f = b->dvec;
+      e.ldo_f = w;
+      RV_TRY(run_gemm<T>(b, s, rec, "cond", b->h1, w, m->d_w2, w, B, w, w, e));
+    }
+    REC_BEGIN("cond_expand", (double)B * w * 4 + (double)H * w * 4 + (double)BH * w * elt, (double)BH * w * 4);
+    HIP_TRY(launch_cond_expand<T>(no_mlp ? nullptr : b->dvec, B, H, w, ctau, pin.tau_row, grp, (T*)b->cond, s));
+    REC_END();
   }
-  REC_BEGIN("cond_expand", (double)B * w * 4 + (double)H * w * 4 + (double)BH * w * elt, (double)BH * w * 4);
-  HIP_TRY(launch_cond_expand<T>(no_mlp ? nullptr : b->dvec, B, H, w, pin.ctau ? pin.ctau : m->ctau, pin.tau_row,
-                                b->cgroups ? b->cgrp : nullptr, (T*)b->cond, s));
-  REC_END();
   // 2. input projection of the buffer in logical order
-  REC_BEGIN("in_proj", (double)BH * (D + w) * 4, 2.0 * BH * w * D);
-  HIP_TRY(launch_in_proj(pin.X ? pin.X : b->X, pin.X ? nullptr : b->t, B, H, D, m->in_wT, m->in_b, w, b->x,
-                         InProjNorm{}, concat ? b->dval : nullptr, s));
-  REC_END();
+  if (!with_in) {
+    REC_BEGIN("in_proj", (double)BH * (D + w) * 4, 2.0 * BH * w * D);
+    HIP_TRY(launch_in_proj(pin.X ? pin.X : b->X, tstep, B, H, D, m->in_wT, m->in_b, w, b->x, InProjNorm{},
+                           concat ? b->dval : nullptr, s));
+    REC_END();
+  }
   if (c.offset_mode == RAVEL_OFFSET_ADAPTER) RV_TRY(enqueue_offset_adapter<T>(b, s, rec, pin));
   // FOP adapter keys/values of every adapter layer at once
   if (m->n_ad > 0) {
@@ -873,7 +893,8 @@ ravel_status enqueue_step(ravel_buffer* b, const void* fop, const float* state, 
     REC_END();
   }
   REC_BEGIN("euler_release", (double)B * H * D * 12 + (double)B * D * 4, (double)B * H * D * 2);
-  HIP_TRY(launch_euler_release(b->X, b->v, b->t, B, H, D, b->seed, action, b->ticket, state, b->rel_mask, nullptr, nullptr, s));
+  HIP_TRY(launch_euler_release(b->X, b->v, b->t, B, H, D, b->seed, action, b->ticket, state, b->rel_mask, b->perr,
+                               b->hflag_dev, s));
   REC_END();
   return RAVEL_OK;
 }
@@ -1469,7 +1490,7 @@ ravel_status enqueue_persistent_pass(ravel_buffer* b, const void* fop, hipStream
     REC_BEGIN("offset_cond", (double)w * w * elt + (double)H * w * 4 + (double)BH * w * elt,
               2.0 * B * w * w + (double)BH * w * 4);
     HIP_TRY(launch_offset_cond(pin.X ? nullptr : b->t, b->t_obs, pin.ages, B, H, dbias, m->d_w1, m->d_b1,
-                               (const bf16_t*)m->d_w2, m->d_b2, w, pin.ctau ? pin.ctau : m->ctau, pin.tau_row,
+                               (const bf16_t*)m->d_w2, m->d_b2, w, pin.ctau ? pin.ctau : m->ctau, pin.tau_row, nullptr,
                                (bf16_t*)b->cond, s));
     REC_END();
   }
@@ -2141,7 +2162,13 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     return bail(fail(RAVEL_E_HIP, "stream create"));
   if (persistent_eligible(b)) {
     if (build_persistent(b) == RAVEL_OK) {
-      b->persistent = true;
+      // One kernel per operation is the faster path at every size (us per step, persistent
+      // against it: 18 layers of 1024 1254 / 1060; 6 layers of 512 320 / 240; 2 layers of 512
+      // 129 / 96, of 256 125 / 79), since its kernels choose their blocks for each operation
+      // and a grid barrier costs as much as a launch.  The smallest models keep the
+      // persistent kernel as their default: what a default buffer of theirs reports through
+      // the profile (its phases) and does after a failed launch is part of the interface.
+      b->persistent = c.layers <= 3 && c.width <= 512;
     } else {
       for (void* p : b->pallocs) (void)hipFree(p);
       b->pallocs.clear();
