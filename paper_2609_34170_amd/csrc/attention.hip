@@ -396,8 +396,10 @@ __global__ __launch_bounds__(NB * 128) void attn_gqa_kernel(AttnArgs a, int chun
   }
 }
 
-// out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s over the key ranges s, in range
-// order, four dims per thread.
+// out = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s over the (at most NS) key ranges s, in
+// range order, four dims per thread.  Every range's loads are in flight together: the
+// launch is one round trip to memory long.
+template <int NS>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_ml, int nsplit, int rows,
                                                            int nq, int hd, bf16_t* __restrict__ out, int ldo) {
@@ -405,36 +407,26 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= (long long)rows * qd) return;
   const int row = (int)(i / qd), c = (int)(i % qd), h = c / hd;
-  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4_t num = zero;
-  float m = -INFINITY, den = 0.f;
-  constexpr int B = 8;  // ranges whose loads are in flight together
-  for (int s0 = 0; s0 < nsplit; s0 += B) {
-    float2 ml[B];
-    f32x4_t o[B];
+  float2 ml[NS];
+  f32x4_t o[NS];
 #pragma unroll
-    for (int s = 0; s < B; ++s) {
-      const bool in = s0 + s < nsplit;
-      const size_t pr = (size_t)(s0 + (in ? s : 0)) * rows + row;
-      ml[s] = *(const float2*)(part_ml + (pr * nq + h) * 2);
-      o[s] = *(const f32x4_t*)(part_o + pr * qd + c);
-      if (!in) ml[s] = float2{-INFINITY, 0.f};
-    }
-    float mx = m;
+  for (int s = 0; s < NS; ++s) {
+    const size_t pr = (size_t)min(s, nsplit - 1) * rows + row;
+    ml[s] = *(const float2*)(part_ml + (pr * nq + h) * 2);
+    o[s] = *(const f32x4_t*)(part_o + pr * qd + c);
+  }
+  __builtin_amdgcn_sched_barrier(0);  // without it the compiler sinks the loads to their uses
+  float mx = ml[0].x;  // every range has a key: finite
 #pragma unroll
-    for (int s = 0; s < B; ++s) mx = fmaxf(mx, ml[s].x);
-    const float corr = __builtin_amdgcn_exp2f(m - mx);  // the first time 2^-inf = 0 (mx is finite: every range has a key)
-    m = mx;
-    den *= corr;
+  for (int s = 1; s < NS; ++s) mx = fmaxf(mx, ml[s].x);
+  f32x4_t num = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) num[k] *= corr;
+  for (int s = 0; s < NS; ++s) {
+    const float wt = s < nsplit ? __builtin_amdgcn_exp2f(ml[s].x - mx) : 0.f;
+    den += wt * ml[s].y;
 #pragma unroll
-    for (int s = 0; s < B; ++s) {
-      const float wt = __builtin_amdgcn_exp2f(ml[s].x - mx);
-      den += wt * ml[s].y;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) num[k] += wt * o[s][k];
-    }
+    for (int k = 0; k < 4; ++k) num[k] += wt * o[s][k];
   }
   const float inv = 1.f / den;
   const u32x2_t wv = {pack_bf16x2(num[0] * inv, num[1] * inv), pack_bf16x2(num[2] * inv, num[3] * inv)};
@@ -473,11 +465,12 @@ static hipError_t launch_gqa(const AttnArgs& a, hipStream_t s) {
   constexpr int TK = tile_keys(HD);
   const int R = a.nq / a.nkv * a.Hq, chunks = (R + 63) / 64;
   if (a.nsplit > 1) {
-    if (a.keys_per_split % TK || !a.part_o || !a.part_ml) return hipErrorInvalidValue;
+    if (a.keys_per_split % TK || a.nsplit > 16 || !a.part_o || !a.part_ml) return hipErrorInvalidValue;
     hipLaunchKernelGGL((attn_gqa_kernel<HD, TK, 4, true>), dim3(blocks_of(a, 64) * a.nsplit), dim3(512), 0, s, a, chunks);
     const long long n = (long long)a.B * a.Hq * a.nq * HD / 4;
-    hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.part_o, a.part_ml,
-                       a.nsplit, a.B * a.Hq, a.nq, HD, (bf16_t*)a.out, a.ldo);
+    const auto combine = a.nsplit <= 4 ? attn_combine_kernel<4> : a.nsplit <= 8 ? attn_combine_kernel<8> : attn_combine_kernel<16>;
+    hipLaunchKernelGGL(combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.part_o, a.part_ml, a.nsplit,
+                       a.B * a.Hq, a.nq, HD, (bf16_t*)a.out, a.ldo);
   } else if (wide(a)) {
     hipLaunchKernelGGL((attn_gqa_kernel<HD, TK, 8, false>), dim3(blocks_of(a, 128)), dim3(1024), 0, s, a, (R + 127) / 128);
   } else {

@@ -164,11 +164,13 @@ template hipError_t launch_adarms<bf16_t>(const float*, int, int, int, const flo
 // threads, 4 columns each, NCH times): the sums of the K ranges, the gated update and the
 // row's sum of squares are formed in registers, so x is read and written once and the
 // normalised row leaves in the same pass.  Bound by the latency of one load round (few
-// rows) or by the partial sums' bytes: 3.3 us after a 3.8 us GEMM at 50 rows x 1024 with
-// 8 ranges, where the last-arriving block's reduction took 8-20 us and the norm 4.7.
+// rows), so every load is issued before anything is added (KS ranges at compile time), or
+// by the partial sums' bytes: 3.4 us after a 4.8 us GEMM at 50 rows x 1024 with 8 ranges
+// (4.5 with four ranges in flight at a time), where the last-arriving block's reduction
+// took 8-20 us and the norm 4.7.
 // ---------------------------------------------------------------------------
-template <int NT, int NCH>
-__global__ __launch_bounds__(NT) void resid_norm_kernel(const float* __restrict__ part, int ksplit, long long zstride,
+template <int NT, int NCH, int KS>
+__global__ __launch_bounds__(NT) void resid_norm_kernel(const float* __restrict__ part, long long zstride,
                                                         float* __restrict__ x, int w, const float* __restrict__ gate,
                                                         const float* __restrict__ gate_scalar,
                                                         const float* __restrict__ scale,
@@ -177,48 +179,48 @@ __global__ __launch_bounds__(NT) void resid_norm_kernel(const float* __restrict_
                                                         bf16_t* __restrict__ y) {
   __shared__ float red[NT / 64];
   const int row = blockIdx.x, tid = threadIdx.x;
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t t[NCH][KS], v[NCH], g[NCH], sc[NCH], sh[NCH];
+  int n[NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    n[c] = min(tid * 4 + c * NT * 4, w - 4);  // past the row: its last columns again, not stored
+    const float* pp = part + (size_t)row * w + n[c];
+#pragma unroll
+    for (int z = 0; z < KS; ++z) t[c][z] = *(const f32x4_t*)(pp + z * zstride);
+    v[c] = *(const f32x4_t*)(x + (size_t)row * w + n[c]);
+    g[c] = sc[c] = sh[c] = zero;
+  }
   const size_t mrow = (size_t)(rowmap ? rowmap[row] : row) * ldm;
   const float* srow = mode == 0 ? scale + mrow : scale;
-  const float* hrow = mode == 0 ? shift + mrow : nullptr;
-  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4_t v[NCH], sc[NCH], sh[NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    if (gate) g[c] = *(const f32x4_t*)(gate + mrow + n[c]);
+    if (y) sc[c] = *(const f32x4_t*)(srow + n[c]);
+    if (y && mode == 0) sh[c] = *(const f32x4_t*)(shift + mrow + n[c]);
+  }
+  // without it the compiler sinks the loads to their uses and keeps four in flight
+  __builtin_amdgcn_sched_barrier(0);
+  if (!gate) {
+    const float th = tanhf(*gate_scalar);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) g[c] = f32x4_t{th, th, th, th};
+  }
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int n = tid * 4 + c * NT * 4;
-    v[c] = sc[c] = sh[c] = zero;
-    if (n >= w) continue;
-    float* xp = x + (size_t)row * w + n;
-    f32x4_t xv = *(const f32x4_t*)xp;
-    f32x4_t g;
-    if (gate) {
-      g = *(const f32x4_t*)(gate + mrow + n);
-    } else {
-      const float t = tanhf(*gate_scalar);
-      g = f32x4_t{t, t, t, t};
-    }
-    if (y) {
-      sc[c] = *(const f32x4_t*)(srow + n);
-      if (hrow) sh[c] = *(const f32x4_t*)(hrow + n);
-    }
-    const float* pp = part + (size_t)row * w + n;
-    f32x4_t sum = zero;
-    for (int z = 0; z < ksplit; z += 4) {  // four ranges' loads in flight, added in range order
-      f32x4_t t[4];
+    f32x4_t sum = t[c][0];  // the ranges in order
 #pragma unroll
-      for (int q = 0; q < 4; ++q) t[q] = z + q < ksplit ? *(const f32x4_t*)(pp + (z + q) * zstride) : zero;
+    for (int z = 1; z < KS; ++z)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum[i] += t[q][i];
-    }
+      for (int i = 0; i < 4; ++i) sum[i] += t[c][z][i];
+    const bool in = tid * 4 + c * NT * 4 < w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      xv[i] = xv[i] + g[i] * sum[i];
-      ss += xv[i] * xv[i];
+      v[c][i] = v[c][i] + g[c][i] * sum[i];
+      if (in) ss += v[c][i] * v[c][i];
     }
-    v[c] = xv;
-    *(f32x4_t*)xp = xv;
+    if (in) *(f32x4_t*)(x + (size_t)row * w + n[c]) = v[c];
   }
   if (!y) return;
   ss = wave_sum(ss);
@@ -232,25 +234,22 @@ __global__ __launch_bounds__(NT) void resid_norm_kernel(const float* __restrict_
   const float r = 1.0f / sqrtf(ss / (float)w + eps);
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int n = tid * 4 + c * NT * 4;
-    if (n >= w) continue;
+    if (tid * 4 + c * NT * 4 >= w) continue;
     float o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = v[c][i] * r * (1.0f + sc[c][i]) + sh[c][i];
-    store4<bf16_t>(y + (size_t)row * w + n, o[0], o[1], o[2], o[3]);
+    store4<bf16_t>(y + (size_t)row * w + n[c], o[0], o[1], o[2], o[3]);
   }
 }
 
-hipError_t launch_resid_norm(const float* part, int ksplit, float* x, int M, int w, const float* gate,
-                             const float* gate_scalar, const float* scale, const float* shift, int ldm, int mode,
-                             const int* rowmap, float eps, bf16_t* y, hipStream_t s) {
-  if (w % 4 || w > kResidNormMaxW || ksplit < 1 || (!gate && !gate_scalar) || ((gate || mode == 0) && ldm % 4) ||
-      ((uintptr_t)part | (uintptr_t)x | (uintptr_t)gate) % 16 || (y && ((uintptr_t)scale | (uintptr_t)shift) % 16))
-    return hipErrorInvalidValue;
+template <int KS>
+static hipError_t launch_resid_norm_ks(const float* part, float* x, int M, int w, const float* gate,
+                                       const float* gate_scalar, const float* scale, const float* shift, int ldm, int mode,
+                                       const int* rowmap, float eps, bf16_t* y, hipStream_t s) {
   const long long zs = (long long)M * w;
-#define RAVEL_RN(NT, NCH)                                                                                       \
-  hipLaunchKernelGGL((resid_norm_kernel<NT, NCH>), dim3(M), dim3(NT), 0, s, part, ksplit, zs, x, w, gate, gate_scalar, \
-                     scale, shift, ldm, mode, rowmap, eps, y)
+#define RAVEL_RN(NT, NCH)                                                                                            \
+  hipLaunchKernelGGL((resid_norm_kernel<NT, NCH, KS>), dim3(M), dim3(NT), 0, s, part, zs, x, w, gate, gate_scalar, scale, \
+                     shift, ldm, mode, rowmap, eps, y)
   if (w <= 256)
     RAVEL_RN(64, 1);
   else if (w <= 512)
@@ -258,11 +257,29 @@ hipError_t launch_resid_norm(const float* part, int ksplit, float* x, int M, int
   else if (w <= 1024)
     RAVEL_RN(256, 1);
   else if (w <= 2048)
-    RAVEL_RN(256, 2);
+    RAVEL_RN(512, 1);
   else
-    RAVEL_RN(256, 4);
+    RAVEL_RN(512, 2);
 #undef RAVEL_RN
   return hipGetLastError();
+}
+
+hipError_t launch_resid_norm(const float* part, int ksplit, float* x, int M, int w, const float* gate,
+                             const float* gate_scalar, const float* scale, const float* shift, int ldm, int mode,
+                             const int* rowmap, float eps, bf16_t* y, hipStream_t s) {
+  if (w % 4 || w < 4 || w > kResidNormMaxW || (!gate && !gate_scalar) || ((gate || mode == 0) && ldm % 4) ||
+      ((uintptr_t)part | (uintptr_t)x | (uintptr_t)gate) % 16 || (y && ((uintptr_t)scale | (uintptr_t)shift) % 16))
+    return hipErrorInvalidValue;
+  switch (ksplit) {  // plan_tile's range counts
+#define RAVEL_RK(KS) \
+  case KS: return launch_resid_norm_ks<KS>(part, x, M, w, gate, gate_scalar, scale, shift, ldm, mode, rowmap, eps, y, s)
+    RAVEL_RK(1);
+    RAVEL_RK(2);
+    RAVEL_RK(4);
+    RAVEL_RK(8);
+#undef RAVEL_RK
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // ---------------------------------------------------------------------------
