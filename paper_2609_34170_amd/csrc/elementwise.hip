@@ -1009,6 +1009,132 @@ hipError_t launch_euler_release(float* X, const float* v, int64_t* t, int B, int
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Output head and Euler update in one launch (bf16 models): v = y W_out^T + b_out for 16
+// slots of one env per block, four waves adding quarters of K through LDS, then the
+// update of those slots' ring elements (or of a chunk's, t = NULL), the release of
+// logical slot 0 and its refill.  The fifth wave draws the refill's noise beside the
+// product: in the update kernel it was a chain of its own (the Box-Muller code read
+// cold), and the product of up to 64 rows ran on one or two blocks.  All loads of a K
+// quarter up to 256 are in flight at once.  Before (GEMM + update) -> now, us: one env of
+// 50 slots x 1024 18.3 -> 7.7, one of 100 x 2048 21.8 -> 9.8.
+// ---------------------------------------------------------------------------
+template <int NF>  // 16-column fragments of the action dims
+__global__ __launch_bounds__(320) void head_euler_kernel(const bf16_t* __restrict__ y, int w,
+                                                         const bf16_t* __restrict__ W, const float* __restrict__ bias,
+                                                         float* __restrict__ v, float* __restrict__ X, int64_t* t, int H,
+                                                         int D, float dt, uint64_t seed, float* __restrict__ action,
+                                                         const float* __restrict__ state,
+                                                         const float* __restrict__ mask, unsigned* ticket,
+                                                         const int* err, int* host_flag) {
+  constexpr int LD = NF * 16 + 4;
+  __shared__ __attribute__((aligned(16))) float part[4][16][LD];
+  __shared__ float noise[NF * 16];
+  const int tiles = (H + 15) / 16;
+  const int e = blockIdx.x / tiles, i0 = (blockIdx.x % tiles) * 16;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // a failed launch before (see euler_release_kernel)
+  if (err && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+    if (i0 == 0 && tid < D) action[(size_t)e * D + tid] = __int_as_float(0x7fc00000);
+    if (host_flag && blockIdx.x == 0 && tid == 0)
+      __hip_atomic_store(host_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return;
+  }
+  const int64_t tt = t ? *t : 0;
+  const int h0 = (int)(tt % H);
+  const int n = min(16, H - i0) * D;  // elements of this block
+  int off[NF];
+  float xv[NF];
+  if (wave < 4) {
+    const int l16 = lane & 15, grp = lane >> 4, steps = w / 128;
+    const bf16_t* pa = y + ((size_t)e * H + min(i0 + l16, H - 1)) * w + wave * (w / 4) + grp * 8;
+    const bf16_t* pb[NF];
+    f32x4_t acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      pb[f] = W + (size_t)min(f * 16 + l16, D - 1) * w + wave * (w / 4) + grp * 8;
+      acc[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    constexpr int U = 8;
+    for (int s0 = 0; s0 < steps; s0 += U) {
+      bf16x8_t af[U], bf[U][NF];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int o = min(s0 + u, steps - 1) * 32;  // past the quarter: its last step again, not added
+        af[u] = *(const bf16x8_t*)(pa + o);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) bf[u][f] = *(const bf16x8_t*)(pb[f] + o);
+      }
+      if (s0 == 0) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+          const int k = tid + q * 256, i = k / D;
+          int ph = i0 + i + h0;
+          if (ph >= H) ph -= H;
+          off[q] = k < n ? (e * H + ph) * D + (k - i * D) : -1;
+          xv[q] = k < n ? X[off[q]] : 0.f;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);  // all loads before the first use
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= steps) break;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[u][f], af[u], acc[f], 0, 0, 0);
+      }
+    }
+    // acc[f][r]: slot i0 + l16, dim f 16 + grp 4 + r
+#pragma unroll
+    for (int f = 0; f < NF; ++f) *(f32x4_t*)&part[wave][l16][f * 16 + grp * 4] = acc[f];
+  } else if (t && i0 == 0 && lane * 4 < D) {
+    float z[4];
+    ring_noise4(seed, e, tt + H, lane, z);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) noise[lane * 4 + q] = z[q];
+  }
+  __syncthreads();
+  if (wave < 4) {
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+      if (off[q] < 0) continue;
+      const int k = tid + q * 256, i = k / D, d = k - i * D;
+      const float vel = ((part[0][i][d] + part[1][i][d]) + (part[2][i][d] + part[3][i][d])) + bias[d];
+      const float xn = euler_sub(xv[q], dt, vel);
+      if (v) v[((size_t)e * H + i0 + i) * D + d] = vel;
+      if (t && i0 + i == 0) {
+        action[(size_t)e * D + d] = state ? xn + mask[d] * state[(size_t)e * D + d] : xn;
+        X[off[q]] = noise[d];
+      } else {
+        X[off[q]] = xn;
+      }
+    }
+  }
+  // every thread of the block has read the step counter; the last block advances it
+  if (t && tid == 0) {
+    if (gridDim.x == 1) {
+      *t = tt + 1;
+    } else if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
+      *ticket = 0u;
+      *t = tt + 1;
+    }
+  }
+}
+
+bool head_euler_ok(int w, int D) { return w % 128 == 0 && D >= 1 && D <= 64; }
+
+hipError_t launch_head_euler(const bf16_t* y, int w, const bf16_t* W, const float* bias, float* v, float* X, int64_t* t,
+                             int B, int H, int D, float dt, uint64_t seed, float* action, const float* state,
+                             const float* mask, unsigned* ticket, const int* err, int* host_flag, hipStream_t s) {
+  if (!head_euler_ok(w, D) || H < 1 || B < 1 || (t && (!action || !ticket)) || ((uintptr_t)y | (uintptr_t)W) % 16 ||
+      (long long)B * H * D > 0x7fffffffll)
+    return hipErrorInvalidValue;
+  const dim3 grid(B * ((H + 15) / 16)), block(320);
+  const auto k = D <= 16 ? head_euler_kernel<1> : D <= 32 ? head_euler_kernel<2> : head_euler_kernel<4>;
+  hipLaunchKernelGGL(k, grid, block, 0, s, y, w, W, bias, v, X, t, H, D, dt, seed, action, state, mask, ticket, err,
+                     host_flag);
+  return hipGetLastError();
+}
+
 __global__ void zero_u32_kernel(unsigned* __restrict__ p, long long n) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;

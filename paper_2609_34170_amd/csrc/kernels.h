@@ -270,6 +270,15 @@ hipError_t launch_euler_release(float* X, const float* v, int64_t* t, int B, int
                                 uint64_t seed, float* action, unsigned* ticket, const float* state,
                                 const float* mask, const int* err, int* host_flag, hipStream_t s);
 
+// The output head and the Euler update in one launch (bf16 models, head_euler_ok): v =
+// y W^T + bias ([D, w] weights; stored where v is given), then the ring's update, release and
+// refill as launch_euler_release (t given), or X[e, i, :] -= dt * v for a chunk in logical
+// order (t = NULL).
+bool head_euler_ok(int w, int D);
+hipError_t launch_head_euler(const bf16_t* y, int w, const bf16_t* W, const float* bias, float* v, float* X, int64_t* t,
+                             int B, int H, int D, float dt, uint64_t seed, float* action, const float* state,
+                             const float* mask, unsigned* ticket, const int* err, int* host_flag, hipStream_t s);
+
 // Zero n 32-bit words on stream s with a kernel.
 hipError_t launch_zero_u32(unsigned* p, long long n, hipStream_t s);
 

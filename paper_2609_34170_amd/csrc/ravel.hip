@@ -564,6 +564,10 @@ struct PassIn {
   const int64_t* ages = nullptr;  // [B] context age per env (device) instead of t - t_obs / 0
   int tau_den = 0;                // with tau_row >= 0: that row's flow time is (tau_row + 1) / tau_den
   bool lead_bias = true;          // add delta_0 to the offset (inference); training uses p / H alone
+  const float* mod_row = nullptr;  // every slot's modulation (one row, all layers), computed before the pass
+  bool kva_ready = false;          // the FOP keys/values of an earlier pass over the same tokens are there
+  float* v = nullptr;              // where the velocities go; NULL: the buffer's own
+  bool head = true;                // false: the caller launches the output head (with the Euler update)
 };
 
 // DynamicVLA-style offset form (App. A.1) on the encoded actions x = W_in a + b_in:
@@ -681,9 +685,9 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   // Envs with equal t_obs have equal delta, so equal cond rows and modulation
   // rows: cond is written once per group (compacted) and the modulation GEMM
   // runs on the groups' rows only.
-  const int* rowmap = b->cgroups ? b->crowmap : nullptr;
+  const int* rowmap = b->cgroups && !pin.mod_row ? b->crowmap : nullptr;
   const int* grp = b->cgroups ? b->cgrp : nullptr;
-  if (b->cgroups) {
+  if (b->cgroups && !pin.mod_row) {
     REC_BEGIN("cond_groups", (double)B * 8 + (double)BH * 4, 0.0);
     // equal context ages give equal offsets (the shared t makes equal t_obs equal ages)
     HIP_TRY(launch_cond_groups(pin.ages ? pin.ages : b->t_obs, B, H, b->cgrp, b->crowmap, b->crows, s));
@@ -694,7 +698,9 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   // width 1024), on a rolling step of at most 64 rows with the input projection too.
   const bool few = sizeof(T) == 2 && !no_mlp && B <= 16 && offset_cond_ok(w, H);
   const bool with_in = few && !b->cgroups && !pin.X && !pin.ages && !pin.ctau && pin.tau_row < 0 && BH <= 64 && w % 64 == 0;
-  if (with_in) {
+  if (pin.mod_row) {
+    // conditioning and modulation are there
+  } else if (with_in) {
     REC_BEGIN("offset_cond_in_proj", (double)w * w * elt + (double)H * w * 4 + (double)BH * w * elt + (double)BH * (D + w) * 4,
               2.0 * B * w * w + (double)BH * w * 4 + 2.0 * BH * w * D);
     HIP_TRY(launch_offset_cond_in_proj(b->t, b->t_obs, B, H, dbias, m->d_w1, m->d_b1, (const bf16_t*)m->d_w2, m->d_b2,
@@ -734,15 +740,16 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   }
   if (c.offset_mode == RAVEL_OFFSET_ADAPTER) RV_TRY(enqueue_offset_adapter<T>(b, s, rec, pin));
   // FOP adapter keys/values of every adapter layer at once
-  if (m->n_ad > 0) {
+  if (m->n_ad > 0 && !pin.kva_ready) {
     GemmArgs e = epi_args(EPI_T);
     e.out_t = b->kva;
     e.ldo_t = m->n_ad * 2 * kvd;
     RV_TRY(run_gemm<T>(b, s, rec, "fop_kv", fop, w, m->kva_w, w, B * c.n_fop, m->n_ad * 2 * kvd, w, e));
   }
   const size_t ctx_layer = (size_t)c.prefix_len * kvd;
-  const int ldm = b->mod_ld;
-  if (b->mod_all) {
+  const int ldm = pin.mod_row ? 0 : b->mod_ld;
+  const float* const mod0 = pin.mod_row ? pin.mod_row : b->mod;
+  if (b->mod_all && !pin.mod_row) {
     // modulation chunks (s1, b1, g1, s2, b2, g2) of every layer and (s_f, b_f) at once
     GemmArgs e = epi_args(EPI_F32);
     e.bias = m->mod_all_b;
@@ -753,7 +760,7 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   }
   // the norm before layer l's attention; layer c.layers: the final norm (mod_all)
   const auto norm1 = [&](int l) {
-    const float* md = b->mod + (size_t)l * 6 * w;
+    const float* md = mod0 + (size_t)l * 6 * w;
     return NormOf{md, md + w, 0};
   };
   const auto adarms = [&](const NormOf& nm, int ld) -> ravel_status {
@@ -766,7 +773,7 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
   if (b->mod_all) RV_TRY(adarms(norm1(0), ldm));
   for (int l = 0; l < c.layers; ++l) {
     const LayerW& L = m->layers[l];
-    const float* mod = b->mod_all ? b->mod + (size_t)l * 6 * w : b->mod;
+    const float* mod = b->mod_all ? mod0 + (size_t)l * 6 * w : b->mod;
     const NormOf norm2{mod + 3 * w, mod + 4 * w, 0};
     const bool ad = L.adapter >= 0 && fop;
     if (!b->mod_all) {
@@ -861,10 +868,10 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
     RV_TRY(run_gemm<T>(b, s, rec, "final_mod", b->cond, w, m->fmod_w, w, BH, 2 * w, w, e));
     RV_TRY(adarms(NormOf{b->fmod, b->fmod + w, 0}, 2 * w));
   }
-  {
+  if (pin.head) {
     GemmArgs e = epi_args(EPI_F32);
     e.bias = m->out_b;
-    e.out_f = b->v;
+    e.out_f = pin.v ? pin.v : b->v;
     e.ldo_f = D;
     RV_TRY(run_gemm<T>(b, s, rec, "out", b->y, w, m->out_w, w, BH, D, w, e));
   }
@@ -881,22 +888,75 @@ ravel_status enqueue_step(ravel_buffer* b, const void* fop, const float* state, 
     HIP_TRY(launch_relative_shift(b->X, b->t, B, H, D, b->rel_mask, state, b->s_prev, b->has_prev, s));
     REC_END();
   }
+  const bool fused = c.model_kind == RAVEL_TRANSFORMER && m->bf16 && head_euler_ok(c.width, D);
   if (c.model_kind == RAVEL_TRANSFORMER) {
+    PassIn pin;
+    pin.head = !fused;
     if (m->bf16)
-      RV_TRY(enqueue_transformer<bf16_t>(b, fop, s, rec, PassIn{}));
+      RV_TRY(enqueue_transformer<bf16_t>(b, fop, s, rec, pin));
     else
-      RV_TRY(enqueue_transformer<float>(b, fop, s, rec, PassIn{}));
+      RV_TRY(enqueue_transformer<float>(b, fop, s, rec, pin));
   } else {
     REC_BEGIN("analytic_velocity", (double)B * H * D * 8, (double)B * H * D * 2);
     HIP_TRY(launch_analytic_velocity(c.model_kind, b->X, b->t, B, H, D, m->analytic, 0.f, state, b->rel_mask, b->v,
                                      s));
     REC_END();
   }
+  if (fused) {
+    REC_BEGIN("head_euler", ((double)B * H * c.width + (double)D * c.width) * 2 + (double)B * H * D * 12 + (double)B * D * 4,
+              2.0 * B * H * D * (c.width + 1));
+    HIP_TRY(launch_head_euler((const bf16_t*)b->y, c.width, (const bf16_t*)m->out_w, m->out_b, b->v, b->X, b->t, B, H, D,
+                              1.0f / (float)H, b->seed, action, state, b->rel_mask, b->ticket, b->perr, b->hflag_dev, s));
+    REC_END();
+    return RAVEL_OK;
+  }
   REC_BEGIN("euler_release", (double)B * H * D * 12 + (double)B * D * 4, (double)B * H * D * 2);
   HIP_TRY(launch_euler_release(b->X, b->v, b->t, B, H, D, b->seed, action, b->ticket, state, b->rel_mask, b->perr,
                                b->hflag_dev, s));
   REC_END();
   return RAVEL_OK;
+}
+
+// Widths whose modulation of up to 64 rows takes the few-row kernels (whole K per block: no
+// workspace of K ranges).
+bool few_row_mod(int w) { return w <= 1024 && w % 128 == 0; }
+
+// Modulation of n Euler steps of a full-horizon chunk: row r of b->mod for the flow time of
+// row r of `table`.  At one flow time and context age 0 every slot of every env has the same
+// conditioning, so a step needs one row (where a rolling step needs one per slot), and the
+// steps' rows share one pass over the modulation weights.
+template <typename T>
+ravel_status enqueue_step_modulation(ravel_buffer* b, const float* table, int n, hipStream_t s) {
+  ravel_model* m = b->m;
+  const ravel_config& c = m->cfg;
+  const int w = c.width;
+  if (c.offset_mode != RAVEL_OFFSET_MLP) {
+    HIP_TRY(launch_offset_value(nullptr, b->t_obs, nullptr, b->B, c.horizon, c.delta_bias, b->dval, s));
+    HIP_TRY(launch_cond_expand<T>(nullptr, 1, n, w, table, -1, nullptr, (T*)b->cond, s));
+  } else if (sizeof(T) == 2) {
+    HIP_TRY(launch_offset_cond(nullptr, b->t_obs, nullptr, 1, n, c.delta_bias, m->d_w1, m->d_b1, (const bf16_t*)m->d_w2,
+                               m->d_b2, w, table, -1, nullptr, (bf16_t*)b->cond, s));
+  } else {
+    HIP_TRY(launch_delta_hidden<T>(nullptr, b->t_obs, nullptr, 1, c.horizon, c.delta_bias, m->d_w1, m->d_b1, w,
+                                   (T*)b->h1, s));
+    GemmArgs e = epi_args(EPI_F32);
+    e.bias = m->d_b2;
+    e.out_f = b->dvec;
+    e.ldo_f = w;
+    RV_TRY(run_gemm<T>(b, s, nullptr, "cond", b->h1, w, m->d_w2, w, 1, w, w, e));
+    HIP_TRY(launch_cond_expand<T>(b->dvec, 1, n, w, table, -1, nullptr, (T*)b->cond, s));
+  }
+  GemmArgs e = epi_args(EPI_F32);
+  e.bias = m->mod_all_b;
+  e.out_f = b->mod;
+  e.ldo_f = b->mod_ld;
+  return run_gemm<T>(b, s, nullptr, "mod_all", b->cond, w, m->mod_all_w, w, n, b->mod_ld, w, e, !few_row_mod(w));
+}
+// bf16: the GEMMs above need no workspace (the buffer's is sized for its own rows)
+bool step_modulation_ok(const ravel_buffer* b) {
+  const ravel_config& c = b->m->cfg;
+  return b->mod_all && !b->persistent &&
+         (!b->m->bf16 || (c.width % 64 == 0 && (c.offset_mode != RAVEL_OFFSET_MLP || offset_cond_ok(c.width, 1))));
 }
 
 // Apply ready context publishes on the step stream (caller holds the mutex).
@@ -2100,6 +2160,8 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
                                  {BH, w, F, false}, {BH, 2 * w, w, false}, {BH, D, w, false},
                                  {B, w, std::max(c.fop_obs_dim, 8), false}, {B, c.n_fop * w, w, false}};
     if (m->n_ad > 0) shapes.push_back({B * c.n_fop, m->n_ad * 2 * kvd, w, false});
+    // a chunk's Euler steps' modulation rows (no K ranges there)
+    if (few_row_mod(w)) shapes.push_back({std::min(BH, 64), (6 * c.layers + 2) * w, w, false});
     if (m->at_kz > 0) {
       shapes.push_back({BH, w, m->at_kz, false});
       shapes.push_back({BH, w / 4, 2 * w, false});
@@ -2344,10 +2406,29 @@ ravel_status ravel_full_denoise(ravel_buffer* b, int32_t steps, const void* fop,
   const size_t bytes = (size_t)B * H * D * 4;
   if (chunk != noise) HIP_TRY(hipMemcpyAsync(chunk, noise, bytes, hipMemcpyDeviceToDevice, s));
   const float dt = 1.0f / (float)steps;
+  const bool tr = c.model_kind == RAVEL_TRANSFORMER;
+  const bool hoist = tr && step_modulation_ok(b);
+  const bool fused = tr && m->bf16 && !b->persistent && head_euler_ok(c.width, D);
+  const int rows = std::min(steps, B * H <= 128 ? B * H : 128);  // modulation rows at a time
+  int row0 = steps;  // first table row whose modulation is in b->mod
   for (int k = 0; k < steps; ++k) {
     // step k: every slot at tau = (steps - k) / steps, row steps - 1 - k of the table
-    if (c.model_kind == RAVEL_TRANSFORMER) {
+    if (tr) {
       PassIn pin;
+      if (hoist) {
+        const int r = steps - 1 - k;
+        if (r < row0) {
+          const int n = std::min(rows, r + 1);
+          row0 = r + 1 - n;
+          if (m->bf16)
+            RV_TRY(enqueue_step_modulation<bf16_t>(b, table + (size_t)row0 * c.width, n, s));
+          else
+            RV_TRY(enqueue_step_modulation<float>(b, table + (size_t)row0 * c.width, n, s));
+        }
+        pin.mod_row = b->mod + (size_t)(r - row0) * b->mod_ld;
+      }
+      pin.kva_ready = k > 0 && !b->persistent;
+      pin.head = !fused;
       pin.X = chunk;
       pin.ctau = table;
       pin.tau_row = steps - 1 - k;
@@ -2362,7 +2443,11 @@ ravel_status ravel_full_denoise(ravel_buffer* b, int32_t steps, const void* fop,
       HIP_TRY(launch_analytic_velocity(c.model_kind, chunk, nullptr, B, H, D, m->analytic,
                                        (float)(steps - k) / (float)steps, nullptr, nullptr, b->v, s));
     }
-    HIP_TRY(launch_euler_chunk(chunk, b->v, B, H, D, dt, s));
+    if (fused)
+      HIP_TRY(launch_head_euler((const bf16_t*)b->y, c.width, (const bf16_t*)m->out_w, m->out_b, nullptr, chunk, nullptr,
+                                B, H, D, dt, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, s));
+    else
+      HIP_TRY(launch_euler_chunk(chunk, b->v, B, H, D, dt, s));
   }
   return RAVEL_OK;
 }
@@ -2384,12 +2469,14 @@ ravel_status ravel_train_loss(ravel_buffer* b, const float* target, const float*
     for (int e = 0; e < B; ++e)
       if (!b->has_ctx[e]) return fail(RAVEL_E_STATE, "env " + std::to_string(e) + " has no context yet");
   }
+  const float* vel = b->v;
   HIP_TRY(launch_train_buffer(target, noise, B, H, D, b->trainX, s));
   if (c.model_kind == RAVEL_TRANSFORMER) {
     PassIn pin;
     pin.X = b->trainX;
     pin.ages = ages;
     pin.lead_bias = false;
+    if (v_out && (uintptr_t)v_out % 16 == 0 && !b->persistent) vel = pin.v = v_out;
     if (b->persistent)
       RV_TRY(enqueue_persistent_pass(b, fop, s, nullptr, pin));
     else if (m->bf16)
@@ -2400,8 +2487,8 @@ ravel_status ravel_train_loss(ravel_buffer* b, const float* target, const float*
     HIP_TRY(launch_analytic_velocity(c.model_kind, b->trainX, nullptr, B, H, D, m->analytic, 0.f, nullptr, nullptr,
                                      b->v, s));
   }
-  HIP_TRY(launch_train_loss(b->v, target, noise, B, H, D, loss, s));
-  if (v_out) HIP_TRY(hipMemcpyAsync(v_out, b->v, (size_t)B * H * D * 4, hipMemcpyDeviceToDevice, s));
+  HIP_TRY(launch_train_loss(vel, target, noise, B, H, D, loss, s));
+  if (v_out && vel != v_out) HIP_TRY(hipMemcpyAsync(v_out, b->v, (size_t)B * H * D * 4, hipMemcpyDeviceToDevice, s));
   return RAVEL_OK;
 }
 
