@@ -415,6 +415,7 @@ struct ravel_buffer {
   bool sync_ctx = false, use_graph = true, debug = false;
   hipStream_t cap_stream = nullptr;
   std::vector<GraphEntry> graphs;
+  GraphEntry last_set{nullptr, nullptr, nullptr, false, nullptr, nullptr};  // pointers of the last step call
   std::map<int, float*> full_tables;  // flow-time conditioning per full-horizon step count
   float* trainX = nullptr;  // [B, H, D] training buffer of ravel_train_loss
   // relative actions: mask [D] (1 = relative dimension), state the buffer was last
@@ -2514,7 +2515,17 @@ static ravel_status step_impl(ravel_buffer* b, const void* fop, const float* sta
     GraphEntry* ge = nullptr;
     for (auto& g : b->graphs)
       if (g.fop == fop && g.state == state && g.action == action && g.persistent == b->persistent) ge = &g;
-    if (!ge) {
+    // a pointer set is captured the second time in a row it is seen: recording and
+    // instantiating costs about as much as the step itself, which a caller that passes
+    // fresh tensors at every step would pay at every step
+    GraphEntry seen{fop, state, action, b->persistent, nullptr, nullptr};
+    const bool again = b->last_set.fop == fop && b->last_set.state == state && b->last_set.action == action &&
+                       b->last_set.persistent == b->persistent;
+    b->last_set = seen;
+    if (!ge && !again) {
+      RV_TRY(b->persistent ? enqueue_persistent_step(b, fop, state, action, s, nullptr)
+                           : enqueue_step(b, fop, state, action, s, nullptr));
+    } else if (!ge) {
       GraphEntry g{fop, state, action, b->persistent, nullptr, nullptr};
       HIP_TRY(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeRelaxed));
       ravel_status st = b->persistent ? enqueue_persistent_step(b, fop, state, action, b->cap_stream, nullptr)
@@ -2528,7 +2539,7 @@ static ravel_status step_impl(ravel_buffer* b, const void* fop, const float* sta
       b->graphs.push_back(g);
       ge = &b->graphs.back();
     }
-    HIP_TRY(hipGraphLaunch(ge->exec, s));
+    if (ge) HIP_TRY(hipGraphLaunch(ge->exec, s));
   } else if (b->persistent) {
     RV_TRY(enqueue_persistent_step(b, fop, state, action, s, nullptr));
   } else {
