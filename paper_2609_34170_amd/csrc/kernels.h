@@ -124,6 +124,32 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// FOP adapters of a few rows with the projections folded into the tokens' keys and values
+// (bf16 models, adapter_fold_ok): for env e and adapter layer a, kw = K W_q and vw = V W_o^T
+// per head, then per layer the scores and softmax (p), and out = p vw^T ([B H][w], fp32).
+// ---------------------------------------------------------------------------
+struct AdapterArgs {
+  int B, H, w, nq, nkv, hd;
+  int F, Jp;              // FOP tokens per env; nq F rounded up to whole 32s
+  int n_ad, ad;           // adapter layers; this one (scores, output)
+  float scale;
+  const bf16_t* kva;      // [B F][n_ad 2 nkv hd]: each adapter's keys, then its values
+  const bf16_t* wqT;      // [n_ad][w][nq hd]: W_q transposed
+  const bf16_t* wo;       // [n_ad][w][nq hd]
+  const bf16_t* y;        // [B H][w] normalised rows
+  bf16_t* kw;             // [B][n_ad][Jp][w], row h F + f
+  bf16_t* vw;             // [B][n_ad][w][Jp]; columns >= nq F zero
+  bf16_t* p;              // [B H][Jp]; columns >= nq F zero
+};
+// w a multiple of 128 up to 1024, hd a multiple of 32 up to 256, up to 32 tokens, nq F <= 128
+bool adapter_fold_ok(int w, int nq, int hd, int n_fop);
+hipError_t launch_adapter_fold(const AdapterArgs& a, hipStream_t s);
+hipError_t launch_adapter_scores(const AdapterArgs& a, hipStream_t s);
+hipError_t launch_adapter_out(const AdapterArgs& a, float* out, hipStream_t s);
+// dst[c, r] = src[r, c] for an R x C bf16 matrix.
+hipError_t launch_transpose_bf16(const bf16_t* src, int R, int C, bf16_t* dst, hipStream_t s);
+
+// ---------------------------------------------------------------------------
 // Element-wise / row kernels
 // ---------------------------------------------------------------------------
 // y[m,:] = T( x/rms(x) * (1 + scale) + shift ), per-row modulation rows of stride ldm

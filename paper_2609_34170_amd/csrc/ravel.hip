@@ -115,6 +115,8 @@ struct ravel_model {
   std::vector<LayerW> layers;
   int n_ad = 0;
   void* kva_w = nullptr;  // [n_ad * 2 kvd, w]
+  void* oa_all = nullptr;  // [n_ad][w, qd]: the adapters' output projections
+  void* qaT_all = nullptr;  // [n_ad][w, qd]: their query projections transposed (bf16, adapter_fold_ok)
   void* fmod_w = nullptr;  // [2w, w]
   float* fmod_b = nullptr;
   void* out_w = nullptr;
@@ -355,6 +357,7 @@ struct ravel_buffer {
   void* att = nullptr;
   void* qa = nullptr;
   void* kva = nullptr;
+  bf16_t *akw = nullptr, *avw = nullptr, *ap = nullptr;  // folded adapters (AdapterArgs kw, vw, p); null: not used
   void* u = nullptr;
   float* v = nullptr;
   float* fmod = nullptr;
@@ -609,6 +612,38 @@ ravel_status enqueue_offset_adapter(ravel_buffer* b, hipStream_t s, KernelRecord
   return RAVEL_OK;
 }
 
+// Folded adapters (adapter.hip) where their weights' pass over every env's tokens costs less
+// than the launches and projections it saves per layer: up to 4 envs of no fewer slots
+// than tokens.  Per step, four launches a layer -> folded (us): 18 layers of 1024, one env
+// 1048 -> 980 (the fold 24, a layer's adapter 22 -> 11); 6 layers, 4 envs 500 -> 489 (the
+// fold 27); 6 layers of 512, one env 233 -> 226; 5 envs of 512 no gain.
+bool fold_adapters(int B, int H, int n_fop) { return B <= 4 && B * H <= 256 && H >= n_fop; }
+
+AdapterArgs adapter_args(const ravel_buffer* b, int ad) {
+  const ravel_model* m = b->m;
+  const ravel_config& c = m->cfg;
+  AdapterArgs a;
+  a.B = b->B;
+  a.H = c.horizon;
+  a.w = c.width;
+  a.nq = c.n_q_heads;
+  a.nkv = c.n_kv_heads;
+  a.hd = c.head_dim;
+  a.F = c.n_fop;
+  a.Jp = (a.nq * a.F + 31) / 32 * 32;
+  a.n_ad = m->n_ad;
+  a.ad = ad;
+  a.scale = 1.0f / sqrtf((float)c.head_dim);
+  a.kva = (const bf16_t*)b->kva;
+  a.wqT = (const bf16_t*)m->qaT_all;
+  a.wo = (const bf16_t*)m->oa_all;
+  a.y = (const bf16_t*)b->y;
+  a.kw = b->akw;
+  a.vw = b->avw;
+  a.p = b->ap;
+  return a;
+}
+
 // The norm that follows a residual update: rows of scale and shift (stride ldm), or a
 // per-feature scale (mode 1); scale = NULL: none.
 struct NormOf {
@@ -746,6 +781,13 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
     e.out_t = b->kva;
     e.ldo_t = m->n_ad * 2 * kvd;
     RV_TRY(run_gemm<T>(b, s, rec, "fop_kv", fop, w, m->kva_w, w, B * c.n_fop, m->n_ad * 2 * kvd, w, e));
+    if (b->akw) {
+      const double J = (double)c.n_q_heads * c.n_fop;
+      REC_BEGIN("adapter_fold", m->n_ad * (2.0 * w * qd + B * 2 * (J * w + (double)c.n_fop * kvd)) * elt,
+                4.0 * B * m->n_ad * J * c.head_dim * w);
+      HIP_TRY(launch_adapter_fold(adapter_args(b, 0), s));
+      REC_END();
+    }
   }
   const size_t ctx_layer = (size_t)c.prefix_len * kvd;
   const int ldm = pin.mod_row ? 0 : b->mod_ld;
@@ -819,7 +861,20 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
     }
     RV_TRY(resid_norm<T>(b, s, rec, "o", b->att, qd, L.o_w, qd, qd, mod + 2 * w, nullptr, ldm, rowmap,
                          ad ? NormOf{L.gamma, nullptr, 1} : norm2));
-    if (ad) {
+    if (ad && b->akw) {
+      const AdapterArgs a = adapter_args(b, L.adapter);
+      const double J = (double)c.n_q_heads * c.n_fop;
+      REC_BEGIN("adapter_scores", (BH * (w + J) + B * J * w) * elt, 2.0 * BH * J * w);
+      HIP_TRY(launch_adapter_scores(a, s));
+      REC_END();
+      REC_BEGIN("adapter_out", (BH * J + B * J * w) * elt + BH * w * 4.0, 2.0 * BH * J * w);
+      HIP_TRY(launch_adapter_out(a, b->gpart, s));
+      REC_END();
+      REC_BEGIN("resid_norm", (double)BH * w * (24 + elt), (double)BH * w * 8);
+      HIP_TRY(launch_resid_norm(b->gpart, 1, b->x, BH, w, nullptr, L.alpha, norm2.scale, norm2.shift, ldm, norm2.mode,
+                                rowmap, c.rms_eps, (bf16_t*)b->y, s));
+      REC_END();
+    } else if (ad) {
       {
         GemmArgs e = epi_args(EPI_T);
         e.out_t = b->qa;
@@ -1906,11 +1961,14 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
     if (ad_of[l] >= 0) {
       ar.want((void**)&Lw.gamma, (size_t)w * 4);
       ar.want(&Lw.qa_w, (size_t)qd * w * E);
-      ar.want(&Lw.oa_w, (size_t)w * qd * E);
       ar.want((void**)&Lw.alpha, 4);
     }
   }
-  if (n_ad > 0) ar.want(&m->kva_w, (size_t)n_ad * 2 * kvd * w * E);
+  if (n_ad > 0) {
+    ar.want(&m->kva_w, (size_t)n_ad * 2 * kvd * w * E);
+    ar.want(&m->oa_all, (size_t)n_ad * w * qd * E);
+    if (m->bf16 && adapter_fold_ok(w, c.n_q_heads, hd, c.n_fop)) ar.want(&m->qaT_all, (size_t)n_ad * w * qd * E);
+  }
   if (c.rope_base < 0.f || c.rope_base != c.rope_base) return bail(fail(RAVEL_E_INVALID, "rope_base must be >= 0"));
   if (c.rope_base > 0.f) ar.want((void**)&m->rope_cs, (size_t)H * hd * 4);
   if (oadapter) {
@@ -1937,6 +1995,7 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
   for (int l = 0; l < L; ++l) {
     m->layers[l].mod_w = (char*)m->mod_all_w + (size_t)l * 6 * w * w * E;
     m->layers[l].mod_b = m->mod_all_b + (size_t)l * 6 * w;
+    if (ad_of[l] >= 0) m->layers[l].oa_w = (char*)m->oa_all + (size_t)ad_of[l] * w * qd * E;
   }
   m->fmod_w = (char*)m->mod_all_w + (size_t)L * 6 * w * w * E;
   m->fmod_b = m->mod_all_b + (size_t)L * 6 * w;
@@ -2034,6 +2093,9 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
       UP((p + "fop.gamma").c_str(), Lw.gamma, false);
       UP((p + "fop.q.w").c_str(), Lw.qa_w, true);
       UP((p + "fop.o.w").c_str(), Lw.oa_w, true);
+      if (m->qaT_all && launch_transpose_bf16((const bf16_t*)Lw.qa_w, qd, w,
+                                              (bf16_t*)m->qaT_all + (size_t)Lw.adapter * w * qd, 0) != hipSuccess)
+        return bail(done(fail(RAVEL_E_HIP, p + "fop.q.w transpose")));
       UP((p + "fop.alpha").c_str(), Lw.alpha, false);
       void* dst = (char*)m->kva_w + (size_t)Lw.adapter * 2 * kvd * w * E;
       UP((p + "fop.kv.w").c_str(), dst, true);
@@ -2149,6 +2211,13 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     ar.want(&b->att, (size_t)BH * qd * E);
     ar.want(&b->qa, (size_t)BH * qd * E);
     if (m->n_ad > 0) ar.want(&b->kva, (size_t)B * c.n_fop * m->n_ad * 2 * kvd * E);
+    if (m->n_ad > 0 && m->qaT_all && fold_adapters(B, H, c.n_fop)) {
+      part_elems = std::max(part_elems, (size_t)BH * w);
+      const size_t Jp = (size_t)(c.n_q_heads * c.n_fop + 31) / 32 * 32;
+      ar.want((void**)&b->akw, (size_t)B * m->n_ad * Jp * w * E);
+      ar.want((void**)&b->avw, (size_t)B * m->n_ad * w * Jp * E);
+      ar.want((void**)&b->ap, (size_t)BH * Jp * E);  // (columns nq n_fop .. Jp of vw and p stay zero)
+    }
     ar.want(&b->u, (size_t)BH * m->Fp * E);  // columns F .. Fp stay zero
     ar.want((void**)&b->fmod, (size_t)BH * 2 * w * 4);
     ar.want(&b->fhid, (size_t)B * w * E);
