@@ -1,0 +1,142 @@
+"""The kernels that few-row and mid-row passes are made of, at the sizes where their tiles,
+fragments and dispatch rules have edges, through the public entry points.
+
+Velocities (not actions, which a step moves by v / H only) against the float64 oracle.
+Bars as elsewhere (TOL_F32, TOL_BF16): at most two layers of about ten bf16-rounded tensors
+each, 2^-9 apiece and independent, give sqrt(20) 2^-9 = 0.9 % in the 2-norm, and the largest
+element over the largest value is about twice that.
+"""
+
+import numpy as np
+import pytest
+
+import synth
+from tests.harness import TOL_BF16, TOL_F32, GpuRoll, have_gpu, rel_err, velocity_parity
+from tests.test_gpu_full import _transformer_case
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+W = synth.workloads
+
+BASE = dict(layers=2, width=256, n_q_heads=4, n_kv_heads=2, head_dim=64, mlp_dim=512, horizon=20, action_dim=7,
+            prefix_len=40, n_fop=4, fop_obs_dim=16, dtype=W.BF16)
+
+
+def _shape(**kw):
+    return synth.RavelShape(name="few_rows", **{**BASE, **kw})
+
+
+def _step_velocities(s, batch):
+    # three steps: launched directly, recorded, replayed
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    velocity_parity(s, wts, batch, list(range(batch)), [0, 1, 2], tol=TOL_F32 if s.dtype == W.F32 else TOL_BF16,
+                    init_tobs=-2, persistent=None if s.dtype == W.F32 else False, sens_report=())
+
+
+@pytest.mark.parametrize("kw,batch", [
+    (dict(n_fop=1), 1),                                            # one token
+    (dict(n_fop=16, horizon=16), 4),                               # a whole fragment, as many slots as tokens, most envs
+    (dict(n_fop=17), 2),                                           # two fragments, 68 of 96 columns
+    (dict(n_fop=32, horizon=33), 1),                               # 128 columns
+    (dict(n_fop=33, horizon=40), 1),                               # 132 columns: separate projections
+    (dict(n_fop=16, horizon=15), 1),                               # fewer slots than tokens: separate projections
+    (dict(n_fop=5), 5),                                            # five envs: separate projections
+    (dict(width=128, n_q_heads=2, n_kv_heads=1, head_dim=32), 3),  # smallest width and head
+    (dict(width=1024, n_q_heads=8, n_kv_heads=1, head_dim=256, n_fop=16, horizon=17), 1),  # largest
+    (dict(width=192), 1),                                          # not a multiple of 128
+])
+def test_adapter_fold_edges(kw, batch):
+    _step_velocities(_shape(**kw), batch)
+
+
+@pytest.mark.parametrize("kw,batch", [
+    (dict(action_dim=1, horizon=1), 1),
+    (dict(action_dim=16, horizon=16), 1),
+    (dict(action_dim=17, horizon=17), 2),
+    (dict(action_dim=33, horizon=48), 1),
+    (dict(action_dim=64, horizon=128), 1),
+    (dict(action_dim=65, horizon=20), 1),    # separate head and update
+    (dict(width=2048, n_q_heads=8, n_kv_heads=2, head_dim=128, mlp_dim=256, layers=1, n_fop=0), 1),  # two K batches
+])
+def test_output_head_and_update_edges(kw, batch):
+    _step_velocities(_shape(**{"n_fop": 0, **kw}), batch)
+
+
+@pytest.mark.parametrize("kw,batch", [
+    (dict(horizon=1), 1),
+    (dict(horizon=32), 1), (dict(horizon=33), 1),      # 32-row tiles end
+    (dict(horizon=64), 1), (dict(horizon=65), 1),      # the few-row kernels end
+    (dict(horizon=43), 3), (dict(horizon=52), 5),      # 129 rows (K ranges 8 -> 4), 260 rows (4 -> 2)
+    (dict(mlp_dim=80), 2), (dict(mlp_dim=1360), 1),    # hidden rows padded to whole K tiles
+    (dict(width=1040, n_q_heads=4, head_dim=64), 1),   # a last column tile that is nearly empty
+])
+def test_tiled_gemm_edges(kw, batch):
+    _step_velocities(_shape(**kw), batch)
+
+
+@pytest.mark.parametrize("hd,prefix,horizon,batch", [
+    (64, 0, 9, 1), (64, 447, 20, 1), (64, 448, 20, 1),     # below and at eight key tiles
+    (128, 1000, 64, 1), (256, 255, 16, 2), (256, 530, 50, 1), (32, 2000, 3, 1),
+])
+def test_attention_key_ranges(hd, prefix, horizon, batch):
+    _step_velocities(_shape(head_dim=hd, prefix_len=prefix, horizon=horizon, layers=1, n_fop=0), batch)
+
+
+@pytest.mark.parametrize("kw,batch", [
+    (dict(horizon=1, action_dim=1, prefix_len=0), 1),
+    (dict(horizon=17, mlp_dim=80, n_fop=3), 1),
+    (dict(horizon=65, n_q_heads=2, n_kv_heads=1, head_dim=128, n_fop=1), 1),
+    (dict(horizon=16, prefix_len=300, head_dim=32, n_kv_heads=4), 5),
+])
+def test_32_bit_models(kw, batch):
+    _step_velocities(_shape(dtype=W.F32, width=128, **kw), batch)
+
+
+@pytest.mark.parametrize("dtype,horizon,batch,S", [
+    (W.BF16, 3, 1, 8),      # more Euler steps than buffer rows: the modulation comes in parts
+    (W.BF16, 20, 4, 5), (W.BF16, 13, 6, 3),
+    (W.F32, 2, 1, 5), (W.F32, 20, 4, 3),
+])
+@pytest.mark.parametrize("offset", [W.OFFSET_MLP, W.OFFSET_CONCAT, W.OFFSET_ADAPTER])
+def test_chunk_modulation_rows(dtype, horizon, batch, S, offset):
+    kw = {**BASE, "dtype": dtype, "horizon": horizon, "offset_mode": offset}
+    _transformer_case("small_bf16", batch, S, np.float64, persistent=None if dtype == W.F32 else False, **kw)
+
+
+def test_velocities_into_memory_of_any_alignment():
+    import torch
+    s = _shape(n_fop=0, action_dim=5)
+    g = GpuRoll(s, synth.draw_weights(s, seed=4, stress=True), 2, 0)
+    for e in range(2):
+        g.set_context(e, *synth.draw_context(s, 0, e, 0), 0)
+    gen = torch.Generator().manual_seed(0)
+    y, n = (torch.randn((2, s.horizon, 5), generator=gen).to(g.dev) for _ in range(2))
+    ages = torch.tensor([1, 3], dtype=torch.int64, device=g.dev)
+    out = []
+    for off in (0, 1):
+        loss, v = torch.empty(2, device=g.dev), torch.empty(2 * s.horizon * 5 + 1, device=g.dev)
+        v = v[off:off + 2 * s.horizon * 5].view(2, s.horizon, 5)
+        g.buf.train_loss(y, n, ages, None, loss, v)
+        torch.cuda.synchronize()
+        out.append((loss.cpu().numpy(), v.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_fresh_buffers_each_step_are_not_recorded_and_give_the_same_actions():
+    import torch
+
+    from paper_2609_34170_amd import ravel
+    s = _shape()
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    a, b = GpuRoll(s, wts, 1, 3), GpuRoll(s, wts, 1, 3)
+    for g in (a, b):
+        g.buf.set_option(ravel.OPT_PERSISTENT, 0)
+        g.set_context(0, *synth.draw_context(s, 0, 0, 0), 0)
+    outs = [torch.empty((1, s.action_dim), device=a.dev) for _ in range(2)]
+    for st in range(8):
+        z = synth.draw_fop_tokens(s, 0, st, batch=1)
+        fop = a.to_dev(z)
+        a.buf.step(fop, outs[st % 2])
+        torch.cuda.synchronize()
+        assert np.array_equal(outs[st % 2].cpu().numpy(), b.step(z)), st
+    assert a.buf.query(ravel.Q_GRAPHS) == 0 and b.buf.query(ravel.Q_GRAPHS) == 1
