@@ -305,6 +305,12 @@ hipError_t launch_head_euler(const bf16_t* y, int w, const bf16_t* W, const floa
                              int B, int H, int D, float dt, uint64_t seed, float* action, const float* state,
                              const float* mask, unsigned* ticket, const int* err, int* host_flag, hipStream_t s);
 
+// First layer of the FOP encoder: hid[r, n] = bf16(gelu_tanh(bf16(obs[r, :]) . W[n, :] + bias[n])).
+// Up to 64 rows of d values (a multiple of 8, 16-byte aligned), w a multiple of 16.
+bool fop_hidden_ok(const float* obs, int B, int d, int w);
+hipError_t launch_fop_hidden(const float* obs, int B, int d, const bf16_t* W, const float* bias, int w, bf16_t* hid,
+                             hipStream_t s);
+
 // Zero n 32-bit words on stream s with a kernel.
 hipError_t launch_zero_u32(unsigned* p, long long n, hipStream_t s);
 

@@ -1786,8 +1786,12 @@ ravel_status fop_encode_impl(ravel_buffer* b, const float* obs, void* fop_tokens
   e2.out_t = fop_tokens;
   e2.ldo_t = c.n_fop * w;
   if (m->bf16) {
-    HIP_TRY(launch_convert<bf16_t>(obs, (bf16_t*)b->obs_t, (long long)B * d, s));
-    RV_TRY(run_gemm<bf16_t>(b, s, nullptr, "fop1", b->obs_t, d, m->f_w1, d, B, w, d, e1));
+    if (fop_hidden_ok(obs, B, d, w)) {
+      HIP_TRY(launch_fop_hidden(obs, B, d, (const bf16_t*)m->f_w1, m->f_b1, w, (bf16_t*)b->fhid, s));
+    } else {
+      HIP_TRY(launch_convert<bf16_t>(obs, (bf16_t*)b->obs_t, (long long)B * d, s));
+      RV_TRY(run_gemm<bf16_t>(b, s, nullptr, "fop1", b->obs_t, d, m->f_w1, d, B, w, d, e1));
+    }
     RV_TRY(run_gemm<bf16_t>(b, s, nullptr, "fop2", b->fhid, w, m->f_w2, w, B, c.n_fop * w, w, e2));
   } else {
     RV_TRY(run_gemm<float>(b, s, nullptr, "fop1", obs, d, m->f_w1, d, B, w, d, e1));

@@ -140,3 +140,28 @@ def test_fresh_buffers_each_step_are_not_recorded_and_give_the_same_actions():
         torch.cuda.synchronize()
         assert np.array_equal(outs[st % 2].cpu().numpy(), b.step(z)), st
     assert a.buf.query(ravel.Q_GRAPHS) == 0 and b.buf.query(ravel.Q_GRAPHS) == 1
+
+
+@pytest.mark.parametrize("obs,batch,offset", [
+    (8, 1, 0), (136, 3, 0), (128, 16, 0), (512, 17, 0), (520, 2, 0),
+    (64, 64, 0), (64, 65, 0),      # the last in one launch, the first of the tiled product
+    (64, 2, 1),                    # observations off a 16-byte boundary: converted first
+])
+def test_encoder_edges(obs, batch, offset):
+    import torch
+    s = _shape(fop_obs_dim=obs)
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    g = GpuRoll(s, wts, batch, 0)
+    x = np.random.default_rng(obs).standard_normal((batch, obs)).astype(np.float32)
+    mem = torch.empty(batch * obs + 1, device=g.dev)[offset:offset + batch * obs].view(batch, obs)
+    mem.copy_(torch.from_numpy(x))
+    out = torch.empty((batch, s.n_fop, s.width), dtype=torch.bfloat16, device=g.dev)
+    g.buf.fop_encode(mem, out)
+    torch.cuda.synchronize()
+    w = {k: np.asarray(v, np.float64) for k, v in wts.items() if k.startswith("fop.")}
+    xb = torch.from_numpy(x).bfloat16().double().numpy()
+    h = xb @ w["fop.w1"].T + w["fop.b1"]
+    h = 0.5 * h * (1 + np.tanh(np.sqrt(2 / np.pi) * (h + 0.044715 * h**3)))
+    ref = (h @ w["fop.w2"].T + w["fop.b2"]).reshape(out.shape)
+    # two rounded tensors: the hidden rows (2^-9 each, independent) and the tokens
+    assert rel_err(out.float().cpu().numpy(), ref) < 2.0**-7
