@@ -275,7 +275,8 @@ ravel_status ravel_debug_state(ravel_buffer* buf, float* X_host, int64_t* t, int
 
 /* Facts about a buffer's execution (for tests and tooling):
  *   RAVEL_Q_GRAPHS      step graphs captured so far (one per (fop, state, action)
- *                       pointer set and execution path while RAVEL_OPT_USE_GRAPH is on);
+ *                       pointer set and execution path while RAVEL_OPT_USE_GRAPH is on;
+ *                       a set's first step is launched directly, its second captures);
  *   RAVEL_Q_PERSISTENT  1 if the transformer layers run as the persistent kernel;
  *   RAVEL_Q_PHASES      phases of that kernel's list (0 on the per-kernel path);
  *   RAVEL_Q_STEPS       steps enqueued (the host's copy of t).

@@ -328,6 +328,8 @@ struct GraphEntry {
   hipGraphExec_t exec;
 };
 
+constexpr size_t kRecentSets = 8;
+
 struct ravel_buffer {
   ravel_model* m = nullptr;
   int B = 0;
@@ -418,7 +420,7 @@ struct ravel_buffer {
   bool sync_ctx = false, use_graph = true, debug = false;
   hipStream_t cap_stream = nullptr;
   std::vector<GraphEntry> graphs;
-  GraphEntry last_set{nullptr, nullptr, nullptr, false, nullptr, nullptr};  // pointers of the last step call
+  std::vector<GraphEntry> recent_sets;  // pointer sets seen once, not captured (at most kRecentSets)
   std::map<int, float*> full_tables;  // flow-time conditioning per full-horizon step count
   float* trainX = nullptr;  // [B, H, D] training buffer of ravel_train_loss
   // relative actions: mask [D] (1 = relative dimension), state the buffer was last
@@ -2588,13 +2590,23 @@ static ravel_status step_impl(ravel_buffer* b, const void* fop, const float* sta
     GraphEntry* ge = nullptr;
     for (auto& g : b->graphs)
       if (g.fop == fop && g.state == state && g.action == action && g.persistent == b->persistent) ge = &g;
-    // a pointer set is captured the second time in a row it is seen: recording and
-    // instantiating costs about as much as the step itself, which a caller that passes
+    // a pointer set is captured the second time it is seen (among the last few): recording
+    // and instantiating costs about as much as the step itself, which a caller that passes
     // fresh tensors at every step would pay at every step
-    GraphEntry seen{fop, state, action, b->persistent, nullptr, nullptr};
-    const bool again = b->last_set.fop == fop && b->last_set.state == state && b->last_set.action == action &&
-                       b->last_set.persistent == b->persistent;
-    b->last_set = seen;
+    bool again = false;
+    if (!ge) {
+      auto& rs = b->recent_sets;
+      const auto same = [&](const GraphEntry& g) {
+        return g.fop == fop && g.state == state && g.action == action && g.persistent == b->persistent;
+      };
+      const auto it = std::find_if(rs.begin(), rs.end(), same);
+      again = it != rs.end();
+      if (again) rs.erase(it);
+      else {
+        if (rs.size() == kRecentSets) rs.erase(rs.begin());
+        rs.push_back(GraphEntry{fop, state, action, b->persistent, nullptr, nullptr});
+      }
+    }
     if (!ge && !again) {
       RV_TRY(b->persistent ? enqueue_persistent_step(b, fop, state, action, s, nullptr)
                            : enqueue_step(b, fop, state, action, s, nullptr));

@@ -122,24 +122,25 @@ def test_velocities_into_memory_of_any_alignment():
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
-def test_fresh_buffers_each_step_are_not_recorded_and_give_the_same_actions():
+@pytest.mark.parametrize("sets,graphs", [(1, 1), (2, 2), (12, 0)])
+def test_a_pointer_set_is_recorded_on_its_second_step(sets, graphs):
     import torch
 
     from paper_2609_34170_amd import ravel
     s = _shape()
     wts = synth.draw_weights(s, seed=4, stress=True)
-    a, b = GpuRoll(s, wts, 1, 3), GpuRoll(s, wts, 1, 3)
+    a, b = GpuRoll(s, wts, 1, 3), GpuRoll(s, wts, 1, 3, use_graph=False)
     for g in (a, b):
         g.buf.set_option(ravel.OPT_PERSISTENT, 0)
         g.set_context(0, *synth.draw_context(s, 0, 0, 0), 0)
-    outs = [torch.empty((1, s.action_dim), device=a.dev) for _ in range(2)]
-    for st in range(8):
+    outs = [torch.empty((1, s.action_dim), device=a.dev) for _ in range(sets)]
+    for st in range(12):  # with 12 sets each is used once
         z = synth.draw_fop_tokens(s, 0, st, batch=1)
-        fop = a.to_dev(z)
-        a.buf.step(fop, outs[st % 2])
+        a.fop.copy_(a.to_dev(z))
+        a.buf.step(a.fop, outs[st % sets])
         torch.cuda.synchronize()
-        assert np.array_equal(outs[st % 2].cpu().numpy(), b.step(z)), st
-    assert a.buf.query(ravel.Q_GRAPHS) == 0 and b.buf.query(ravel.Q_GRAPHS) == 1
+        assert np.array_equal(outs[st % sets].cpu().numpy(), b.step(z)), st
+    assert a.buf.query(ravel.Q_GRAPHS) == graphs
 
 
 @pytest.mark.parametrize("obs,batch,offset", [
