@@ -344,7 +344,8 @@ ravel_status ravel_full_denoise(ravel_buffer* buf, int32_t steps, const void* fo
  *   target, noise: [B, H, D_a] fp32, device (slot i = the action i+1 steps after t_a);
  *   ages: [B] int64, device, context age p = t_a - t_o per sample;
  *   fop_tokens: as ravel_step; loss_out: [B] fp32, device;
- *   v_out: optional [B, H, D_a] fp32, device: the predicted velocities (NULL: none).
+ *   v_out: optional [B, H, D_a] fp32, device: the predicted velocities (NULL: none; may be
+ *   target or noise itself).
  * Context publications are applied first as ravel_step applies them.  Does not touch the
  * ring or t; shares the buffer's activations with ravel_step (no overlap on one buffer).
  * No backward pass.  Errors: RAVEL_E_INVALID (null pointers, missing FOP tokens),

@@ -975,6 +975,10 @@ ravel_status enqueue_step(ravel_buffer* b, const void* fop, const float* state, 
   return RAVEL_OK;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // Widths whose modulation of up to 64 rows takes the few-row kernels (whole K per block: no
 // workspace of K ranges).
 bool few_row_mod(int w) { return w <= 1024 && w % 128 == 0; }
@@ -2552,7 +2556,12 @@ ravel_status ravel_train_loss(ravel_buffer* b, const float* target, const float*
     pin.X = b->trainX;
     pin.ages = ages;
     pin.lead_bias = false;
-    if (v_out && (uintptr_t)v_out % 16 == 0 && !b->persistent) vel = pin.v = v_out;
+    // the head may write v_out itself unless that would touch what the loss kernel reads or
+    // writes after it: v_out in place of an input is copied once the loss is there
+    const size_t bytes = (size_t)B * H * D * 4;
+    const bool apart = !overlap(v_out, bytes, target, bytes) && !overlap(v_out, bytes, noise, bytes) &&
+                       !overlap(v_out, bytes, loss, (size_t)B * 4);
+    if (v_out && (uintptr_t)v_out % 16 == 0 && apart && !b->persistent) vel = pin.v = v_out;
     if (b->persistent)
       RV_TRY(enqueue_persistent_pass(b, fop, s, nullptr, pin));
     else if (m->bf16)

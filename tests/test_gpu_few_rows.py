@@ -122,6 +122,34 @@ def test_velocities_into_memory_of_any_alignment():
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("shape_kw", [dict(n_fop=0), dict(n_fop=0, dtype=W.F32, width=128)])
+@pytest.mark.parametrize("where", ["target", "noise", "between"])
+def test_velocities_in_place_of_an_input(shape_kw, where):
+    """v_out over target, over noise, and over the end of one and the start of the other:
+    the loss and the velocities are those of a call with memory of its own."""
+    import torch
+    s = _shape(**shape_kw)
+    g = GpuRoll(s, synth.draw_weights(s, seed=4, stress=True), 2, 0)
+    g.buf.set_option(g.rv.OPT_PERSISTENT, 0)
+    for e in range(2):
+        g.set_context(e, *synth.draw_context(s, 0, e, 0), 0)
+    gen = torch.Generator().manual_seed(0)
+    n, shp = 2 * s.horizon * s.action_dim, (2, s.horizon, s.action_dim)
+    data = torch.randn(2 * n, generator=gen).to(g.dev)  # target, then noise
+    ages = torch.tensor([1, 3], dtype=torch.int64, device=g.dev)
+    out = []
+    for own in (True, False):
+        mem = data.clone()
+        at = {"target": 0, "noise": n, "between": n // 2 // 4 * 4}[where]
+        v = torch.empty(shp, device=g.dev) if own else mem[at:at + n].view(shp)
+        loss = torch.empty(2, device=g.dev)
+        g.buf.train_loss(mem[:n].view(shp), mem[n:].view(shp), ages, None, loss, v)
+        torch.cuda.synchronize()
+        out.append((loss.cpu().numpy(), v.cpu().numpy()))
+    assert np.array_equal(out[0][1], out[1][1])
+    assert np.array_equal(out[0][0], out[1][0])
+
+
 @pytest.mark.parametrize("sets,graphs", [(1, 1), (2, 2), (12, 0)])
 def test_a_pointer_set_is_recorded_on_its_second_step(sets, graphs):
     import torch
