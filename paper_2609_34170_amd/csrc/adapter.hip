@@ -4,15 +4,28 @@
 // tokens') do not depend on x, so per head KW = K W_q (n_fop x w) and VW = V W_o^T (w x
 // n_fop) are formed once per step for every adapter layer, in one launch off the layers'
 // chain, and a layer is left with the scores y KW^T and their softmax (one launch), P VW and
-// the residual/norm kernel, over nq n_fop rows of weights instead of 2 nq hd.  Same
-// accumulation (fp32) and as many bf16 roundings: KW and VW in place of q and the
-// attention rows.
+// the residual/norm kernel, over nq n_fop rows of weights instead of 2 nq hd.
+//
+// Precision: KW is rounded to bf16 once, as q is otherwise.  VW and P are held as two bf16
+// parts (value, remainder): VW is a sum over the head that the softmax then averages, so
+// that rounding it (where otherwise the averaged attention rows are) cannot be undone by
+// tokens whose values cancel, and a chunk's Euler steps would all share its rounding.  Errors of
+// velocities and chunks against 64 bits, folded over unfolded, 60 inputs: one part each
+// +0.7 +-0.2 % (2 layers of 1024), +0.4 +-0.1 (6 layers, 4 envs), +1.9 +-0.3 (chunk, 4 layers of
+// 1024), +4.1 +-0.9 (chunk, 4 layers of 512); two parts -1.3, -1.5, -0.5 and -1.9 %.  The
+// remainders cost 0.8 us a layer (18 layers of 1024, one env: 971 -> 978 us a step).
 #include "kernels.h"
 
 namespace ravel {
 
 bool adapter_fold_ok(int w, int nq, int hd, int n_fop) {
   return w % 128 == 0 && w <= 1024 && hd % 32 == 0 && hd <= 256 && n_fop >= 1 && n_fop <= 32 && nq * n_fop <= 128;
+}
+
+// What bf16(x) leaves of x; 0 where that is not finite.
+RAVEL_DEV float remainder_of(float x) {
+  const float h = bf16_to_f32(f32_to_bf16(x));
+  return fabsf(h) < INFINITY ? x - h : 0.f;
 }
 
 // KW[e][a][h F + f][n] = sum_d K[f][d] W_q[h hd + d][n], VW[e][a][n][h F + f] = sum_d V[f][d]
@@ -61,13 +74,15 @@ __global__ __launch_bounds__(256) void adapter_fold_kernel(AdapterArgs a) {
 #pragma unroll
         for (int f = 0; f < FR; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][f], wf[s], acc[f], 0, 0, 0);
     // acc[f][r]: token 16 f + 4 grp + r, column n0 + l16
-    bf16_t* vr = a.vw + (ea * a.w + n0 + l16) * a.Jp + h * a.F;
+    bf16_t* vr = a.vw + (ea * a.w + n0 + l16) * 2 * a.Jp + h * a.F;
 #pragma unroll
     for (int f = 0; f < FR; ++f)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int t = f * 16 + grp * 4 + r;
-        if (t < a.F) vr[t] = f32_to_bf16(acc[f][r]);
+        if (t >= a.F) continue;
+        vr[t] = f32_to_bf16(acc[f][r]);
+        vr[a.Jp + t] = f32_to_bf16(remainder_of(acc[f][r]));
       }
   }
 }
@@ -121,33 +136,47 @@ __global__ __launch_bounds__(256) void adapter_scores_kernel(AdapterArgs a) {
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   if (i0 + i >= a.H) return;
-  bf16_t* pr = a.p + ((size_t)e * a.H + i0 + i) * a.Jp + h * a.F;
+  bf16_t* pr = a.p + ((size_t)e * a.H + i0 + i) * 2 * a.Jp + h * a.F;
 #pragma unroll
-  for (int f = 0; f < FR; ++f)
-    if (f * 16 + c < a.F) pr[f * 16 + c] = f32_to_bf16(s[f] / sum);
+  for (int f = 0; f < FR; ++f) {
+    if (f * 16 + c >= a.F) continue;
+    const float p = s[f] / sum;
+    pr[f * 16 + c] = f32_to_bf16(p);
+    pr[a.Jp + f * 16 + c] = f32_to_bf16(remainder_of(p));
+  }
 }
 
-// out = P VW^T (fp32 rows; the residual kernel adds them and normalises): 16 rows of one env and
-// 64 columns per block, 16 columns per wave.  A block that owned whole rows, norm
-// included, pulled 256 KB through one CU: 18.8 us, against 3.5 and 3.4 for the two.
+// out = P VW^T (fp32 rows; the residual kernel adds them and normalises), the product of the two
+// remainders left out: 16 rows of one env and 64 columns per block, 16 columns per wave.  A
+// block that owned whole rows, norm included, pulled 256 KB through one CU: 18.8 us, against
+// 3.5 and 3.4 for the two (one part each).
 __global__ __launch_bounds__(256) void adapter_out_kernel(AdapterArgs a, float* __restrict__ out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, grp = lane >> 4;
   const int i0 = blockIdx.x * 16, n0 = blockIdx.y * 64 + wave * 16, e = blockIdx.z, steps = a.Jp / 32;
   const size_t row = (size_t)e * a.H + min(i0 + l16, a.H - 1);
-  const bf16_t* pp = a.p + row * a.Jp + grp * 8;
-  const bf16_t* pv = a.vw + (((size_t)e * a.n_ad + a.ad) * a.w + n0 + l16) * a.Jp + grp * 8;
-  bf16x8_t pf[4], vf[4];
+  const bf16_t* pp = a.p + row * 2 * a.Jp + grp * 8;
+  const bf16_t* pv = a.vw + (((size_t)e * a.n_ad + a.ad) * a.w + n0 + l16) * 2 * a.Jp + grp * 8;
+  bf16x8_t pf[4][2], vf[4][2];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {  // nq n_fop <= 128: at most 4 steps
     const int o = min(s, steps - 1) * 32;
-    pf[s] = *(const bf16x8_t*)(pp + o);
-    vf[s] = *(const bf16x8_t*)(pv + o);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      pf[s][q] = *(const bf16x8_t*)(pp + q * a.Jp + o);
+      vf[s][q] = *(const bf16x8_t*)(pv + q * a.Jp + o);
+    }
   }
   __builtin_amdgcn_sched_barrier(0);
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f}, rem = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < 4; ++s)
-    if (s < steps) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s], pf[s], acc, 0, 0, 0);
+    if (s < steps) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][0], pf[s][0], acc, 0, 0, 0);
+      rem = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][1], pf[s][0], rem, 0, 0, 0);
+      rem = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][0], pf[s][1], rem, 0, 0, 0);
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] += rem[r];
   if (i0 + l16 < a.H) *(f32x4_t*)(out + row * a.w + n0 + grp * 4) = acc;
 }
 

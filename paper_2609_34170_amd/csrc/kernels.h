@@ -138,8 +138,8 @@ struct AdapterArgs {
   const bf16_t* wo;       // [n_ad][w][nq hd]
   const bf16_t* y;        // [B H][w] normalised rows
   bf16_t* kw;             // [B][n_ad][Jp][w], row h F + f
-  bf16_t* vw;             // [B][n_ad][w][Jp]; columns >= nq F zero
-  bf16_t* p;              // [B H][Jp]; columns >= nq F zero
+  bf16_t* vw;             // [B][n_ad][w][2 Jp]: values, then their remainders; columns nq F .. Jp of both zero
+  bf16_t* p;              // [B H][2 Jp]: the same
 };
 // w a multiple of 128 up to 1024, hd a multiple of 32 up to 256, up to 32 tokens, nq F <= 128
 bool adapter_fold_ok(int w, int nq, int hd, int n_fop);

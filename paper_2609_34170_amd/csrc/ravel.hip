@@ -866,10 +866,10 @@ ravel_status enqueue_transformer(ravel_buffer* b, const void* fop, hipStream_t s
     if (ad && b->akw) {
       const AdapterArgs a = adapter_args(b, L.adapter);
       const double J = (double)c.n_q_heads * c.n_fop;
-      REC_BEGIN("adapter_scores", (BH * (w + J) + B * J * w) * elt, 2.0 * BH * J * w);
+      REC_BEGIN("adapter_scores", (BH * (w + 2 * J) + B * J * w) * elt, 2.0 * BH * J * w);
       HIP_TRY(launch_adapter_scores(a, s));
       REC_END();
-      REC_BEGIN("adapter_out", (BH * J + B * J * w) * elt + BH * w * 4.0, 2.0 * BH * J * w);
+      REC_BEGIN("adapter_out", 2 * (BH * J + B * J * w) * elt + BH * w * 4.0, 6.0 * BH * J * w);
       HIP_TRY(launch_adapter_out(a, b->gpart, s));
       REC_END();
       REC_BEGIN("resid_norm", (double)BH * w * (24 + elt), (double)BH * w * 8);
@@ -2225,8 +2225,8 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
       part_elems = std::max(part_elems, (size_t)BH * w);
       const size_t Jp = (size_t)(c.n_q_heads * c.n_fop + 31) / 32 * 32;
       ar.want((void**)&b->akw, (size_t)B * m->n_ad * Jp * w * E);
-      ar.want((void**)&b->avw, (size_t)B * m->n_ad * w * Jp * E);
-      ar.want((void**)&b->ap, (size_t)BH * Jp * E);  // (columns nq n_fop .. Jp of vw and p stay zero)
+      ar.want((void**)&b->avw, 2 * (size_t)B * m->n_ad * w * Jp * E);  // values and remainders
+      ar.want((void**)&b->ap, 2 * (size_t)BH * Jp * E);  // (columns nq n_fop .. Jp of vw and p stay zero)
     }
     ar.want(&b->u, (size_t)BH * m->Fp * E);  // columns F .. Fp stay zero
     ar.want((void**)&b->fmod, (size_t)BH * 2 * w * 4);

@@ -49,6 +49,43 @@ def test_adapter_fold_edges(kw, batch):
     _step_velocities(_shape(**kw), batch)
 
 
+@pytest.mark.parametrize("batch", [1, 4, 5])  # folded, folded, separate projections
+def test_adapter_of_tokens_whose_values_cancel(batch):
+    """Two tokens of equal keys and values A + d, -A + d (d = A / 128, all exact in bf16): the
+    attention row is d, while each token's own contribution is 128 times larger.  Rounding
+    those contributions to bf16 (2^-9) would leave errors of 2^-9 128 / sqrt(2 . 3) = 10 % of
+    the adapter's output; with their remainders kept the bar is that of every bf16 case."""
+    from oracle.expert import Expert
+    from oracle.training import expert_velocity, training_loss
+    from tests.test_gpu_train import gpu_train
+    s = _shape(n_fop=2)
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    rng = np.random.default_rng(1)
+    qd, kvd, w = 256, 128, s.width
+    kv = np.zeros((2 * kvd, w), np.float32)
+    kv[kvd:, 0], kv[kvd:, 1] = rng.choice([-1.0, 1.0], kvd), rng.choice([-1.0, 1.0], kvd)
+    wts["layers.1.fop.kv.w"] = kv
+    wts["layers.1.fop.o.w"] = W.bf16_round((64 * rng.standard_normal((w, qd))).astype(np.float32))
+    wts["layers.1.fop.alpha"] = np.full(1, 5.0, np.float32)
+    z = np.zeros((batch, 2, w), np.float32)
+    z[:, 0, 0], z[:, 1, 0], z[:, :, 1] = 1.0, -1.0, 2.0**-7
+    g = GpuRoll(s, wts, batch, 0)
+    g.buf.set_option(g.rv.OPT_PERSISTENT, 0) if batch * s.horizon <= 64 else None
+    ctx = [synth.draw_context(s, 0, e, 0) for e in range(batch)]
+    for e in range(batch):
+        g.set_context(e, *ctx[e], 0)
+    target, noise = (rng.standard_normal((batch, s.horizon, s.action_dim)).astype(np.float32) for _ in range(2))
+    ages = list(range(batch))
+    _, v = gpu_train(g, target, noise, ages, z)
+    ex = Expert(s, wts, np.float64)
+    for e in range(batch):
+        _, ref = training_loss(expert_velocity(ex, *ctx[e], ages[e], z[e]), target[e].astype(np.float64),
+                               noise[e].astype(np.float64))
+        err = rel_err(v[e], ref)
+        print(f"env {e} of {batch}: velocity error {err:.3e}")
+        assert err <= TOL_BF16
+
+
 @pytest.mark.parametrize("kw,batch", [
     (dict(action_dim=1, horizon=1), 1),
     (dict(action_dim=16, horizon=16), 1),
