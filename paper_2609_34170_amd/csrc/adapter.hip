@@ -7,9 +7,9 @@
 // the residual/norm kernel, over nq n_fop rows of weights instead of 2 nq hd.
 //
 // Precision: KW is rounded to bf16 once, as q is otherwise.  VW and P are held as two bf16
-// parts (value, remainder): VW is a sum over the head that the softmax then averages, so
-// that rounding it (where otherwise the averaged attention rows are) cannot be undone by
-// tokens whose values cancel, and a chunk's Euler steps would all share its rounding.  Errors of
+// parts (value, remainder): otherwise it is the attention rows that are rounded, after the
+// softmax has averaged the tokens; rounding every token's VW instead leaves its error where
+// the tokens' values cancel, and the same error in all Euler steps of a chunk.  Errors of
 // velocities and chunks against 64 bits, folded over unfolded, 60 inputs: one part each
 // +0.7 +-0.2 % (2 layers of 1024), +0.4 +-0.1 (6 layers, 4 envs), +1.9 +-0.3 (chunk, 4 layers of
 // 1024), +4.1 +-0.9 (chunk, 4 layers of 512); two parts -1.3, -1.5, -0.5 and -1.9 %.  The
