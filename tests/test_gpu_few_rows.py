@@ -187,8 +187,8 @@ def test_velocities_in_place_of_an_input(shape_kw, where):
     assert np.array_equal(out[0][0], out[1][0])
 
 
-@pytest.mark.parametrize("sets,graphs", [(1, 1), (2, 2), (12, 0)])
-def test_a_pointer_set_is_recorded_on_its_second_step(sets, graphs):
+@pytest.mark.parametrize("sets,rounds,graphs", [(1, 12, 1), (2, 6, 2), (12, 1, 0), (9, 2, 9), (12, 3, 12)])
+def test_a_pointer_set_is_recorded_on_its_second_step(sets, rounds, graphs):
     import torch
 
     from paper_2609_34170_amd import ravel
@@ -199,7 +199,7 @@ def test_a_pointer_set_is_recorded_on_its_second_step(sets, graphs):
         g.buf.set_option(ravel.OPT_PERSISTENT, 0)
         g.set_context(0, *synth.draw_context(s, 0, 0, 0), 0)
     outs = [torch.empty((1, s.action_dim), device=a.dev) for _ in range(sets)]
-    for st in range(12):  # with 12 sets each is used once
+    for st in range(sets * rounds):
         z = synth.draw_fop_tokens(s, 0, st, batch=1)
         a.fop.copy_(a.to_dev(z))
         a.buf.step(a.fop, outs[st % sets])
