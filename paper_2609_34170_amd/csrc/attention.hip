@@ -271,14 +271,16 @@ __global__ __launch_bounds__(NB * 128) void attn_gqa_kernel(AttnArgs a, int chun
         float mx = fmaxf(lmx, __shfl_xor(lmx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float mnew = mx > mrow + kLazy ? mx : mrow;
-        const float corr = __builtin_amdgcn_exp2f(mrow - mnew);
+        const float corr = mrow == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrow - mnew);
         mrow = mnew;
         lrow *= corr;
         if (grp == 0) lds_write_b32(corr0 + ((buf * NB + sub) * 16 + l16) * 4, __float_as_uint(corr));
       }
       if (lane == 0) lds_write_b32(flag0 + (buf * NB + sub) * 4, move ? 1u : 0u);
+      // a row without a finite score so far (keys whose products overflow): probabilities 0
+      const float mref = mrow == -INFINITY ? 0.f : mrow;
 #pragma unroll
-      for (int r = 0; r < 4 * NS; ++r) x[r] = __builtin_amdgcn_exp2f(x[r] - mrow);
+      for (int r = 0; r < 4 * NS; ++r) x[r] = __builtin_amdgcn_exp2f(x[r] - mref);
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
         lrow += ((x[8 * h] + x[8 * h + 1]) + (x[8 * h + 2] + x[8 * h + 3])) +
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
     o[s] = *(const f32x4_t*)(part_o + pr * qd + c);
   }
   __builtin_amdgcn_sched_barrier(0);  // without it the compiler sinks the loads to their uses
-  float mx = ml[0].x;  // every range has a key: finite
+  float mx = ml[0].x;  // -infinity for a range without a finite score: weight 0
 #pragma unroll
   for (int s = 1; s < NS; ++s) mx = fmaxf(mx, ml[s].x);
   f32x4_t num = {0.f, 0.f, 0.f, 0.f};

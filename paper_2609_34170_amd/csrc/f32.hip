@@ -208,12 +208,14 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int chunks) {
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mnew = fmaxf(m, mx);  // finite: the block has a key
-    const float corr = expf(m - mnew);
+    const float mnew = fmaxf(m, mx);
+    // without a finite score so far (keys whose products overflow): probabilities 0
+    const float mref = mnew == -INFINITY ? 0.f : mnew;
+    const float corr = expf(m - mref);
     float p[4], ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = expf(x[r] - mnew);
+      p[r] = expf(x[r] - mref);
       ps += p[r];
     }
     ps += __shfl_xor(ps, 16, 64);

@@ -119,6 +119,46 @@ def test_attention_key_ranges(hd, prefix, horizon, batch):
     _step_velocities(_shape(head_dim=hd, prefix_len=prefix, horizon=horizon, layers=1, n_fop=0), batch)
 
 
+@pytest.mark.parametrize("kw,batch,dead", [
+    (dict(prefix_len=200), 1, (0, 64)),                 # the first key tile
+    (dict(prefix_len=1000), 1, (448, 640)),             # whole tiles at the start of a key range
+    (dict(prefix_len=200, head_dim=256, n_kv_heads=1), 6, (0, 32)),
+    (dict(prefix_len=130, horizon=100, n_kv_heads=1), 40, (0, 64)),   # 128-row chunks
+    (dict(prefix_len=90, dtype=W.F32, width=128), 1, (16, 32)),  # a wave's first keys
+])
+def test_keys_whose_scores_overflow(kw, batch, dead):
+    """Queries of positive entries and a run of prefix keys near the largest negative bf16: their
+    scores are -infinity in 32 bits, their weights 0 (exp of -1e40 in the oracle), and the
+    other keys' softmax is what it is without them."""
+    from oracle.expert import Expert
+    from oracle.training import expert_velocity, training_loss
+    from tests.test_gpu_train import gpu_train
+    s = _shape(layers=1, n_fop=0, **kw)
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    w = s.width
+    wts["layers.0.mod.w"][:2 * w] = 0.0  # attention norm: scale -1, shift 1
+    wts["layers.0.mod.b"][:2 * w] = np.repeat(np.float32([-1.0, 1.0]), w)
+    qd = s.n_q_heads * s.head_dim
+    wts["layers.0.qkv.w"][:qd] = np.abs(wts["layers.0.qkv.w"][:qd])
+    g = GpuRoll(s, wts, batch, 0)
+    if s.dtype == W.BF16 and batch * s.horizon <= 64:
+        g.buf.set_option(g.rv.OPT_PERSISTENT, 0)
+    ctx = []
+    for e in range(batch):
+        k, v = synth.draw_context(s, 0, e, 0)
+        k[:, dead[0]:dead[1]] = -3e38
+        ctx.append((k, v))
+        g.set_context(e, k, v, 0)
+    rng = np.random.default_rng(1)
+    target, noise = (rng.standard_normal((batch, s.horizon, s.action_dim)).astype(np.float32) for _ in range(2))
+    _, got = gpu_train(g, target, noise, [1] * batch)
+    ex = Expert(s, wts, np.float64)
+    for e in {0, batch - 1}:
+        _, ref = training_loss(expert_velocity(ex, *ctx[e], 1, None), target[e].astype(np.float64),
+                               noise[e].astype(np.float64))
+        assert rel_err(got[e], ref) <= (TOL_F32 if s.dtype == W.F32 else TOL_BF16), e
+
+
 @pytest.mark.parametrize("kw,batch", [
     (dict(horizon=1, action_dim=1, prefix_len=0), 1),
     (dict(horizon=17, mlp_dim=80, n_fop=3), 1),
