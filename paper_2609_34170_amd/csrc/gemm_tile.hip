@@ -85,11 +85,20 @@ hipError_t launch_gemm_tile(GemmArgs a, const TilePlan& p, hipStream_t s) {
   if (a.m_rows) {
     // the distinct modulation rows (a device count) times many columns: a fixed grid of
     // two blocks per CU walks the live items, so each weight panel is fetched once per
-    // row tile and XCD and dead row tiles cost nothing
+    // row tile and XCD and dead row tiles cost nothing.  Tiles of 128 columns read fewer bytes
+    // per product, and eight waves (two blocks: four per SIMD) hide each other's waits;
+    // where one row of them would leave CUs idle, of 64 columns.  us, 128 / 64 columns, by
+    // live rows: 112640 x 1024 50 rows 62 / 66, 250 111 / 136, 500 206 / 249; 28672 x 2048 100 rows
+    // 46 / 41, 200 51 / 62, 300 80 / 87; 38912 x 1024 150 rows 47 / 42, 250 53 / 52, 500 75 / 94;
+    // 19456 x 512 48 rows 12.8 / 11.9, 160 17.6 / 19.9.
     if (a.mode != EPI_F32 || a.ksplit != 1) return hipErrorInvalidValue;
-    const int items = items_of(T128x64, a.M, a.N);
-    hipLaunchKernelGGL((gemm_tile_kernel<128, 64, 2, 2, 3, EPI_F32, true>), dim3(items < 512 ? items : 512), dim3(256),
-                       0, s, a);
+    const bool wide = items_of(T128x128, 1, a.N) >= kTargetItems;
+    const int items = items_of(wide ? T128x128 : T128x64, a.M, a.N);
+    const dim3 grid(items < 512 ? items : 512);
+    if (wide)
+      hipLaunchKernelGGL((gemm_tile_kernel<128, 128, 4, 2, 2, EPI_F32, true>), grid, dim3(512), 0, s, a);
+    else
+      hipLaunchKernelGGL((gemm_tile_kernel<128, 64, 2, 2, 3, EPI_F32, true>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
   }
   switch (a.mode) {

@@ -111,6 +111,19 @@ def test_tiled_gemm_edges(kw, batch):
     _step_velocities(_shape(**kw), batch)
 
 
+@pytest.mark.parametrize("layers,horizon,batch,period", [
+    (8, 25, 6, 3),   # modulation of 25600 columns: tiles of 64 columns
+    (9, 25, 6, 3),   # of 28672: the first of tiles of 128 columns; 50 to 75 live rows of 150
+    (9, 64, 5, 5),   # 128 to 320 live rows: whole row tiles and remainders
+])
+def test_modulation_of_distinct_conditionings(layers, horizon, batch, period):
+    s = _shape(layers=layers, width=512, horizon=horizon, mlp_dim=128, n_fop=0, n_kv_heads=4)
+    wts = synth.draw_weights(s, seed=4, stress=True)
+    # the file's bar is for two layers; the errors of more add up as their square root
+    velocity_parity(s, wts, batch, [0, batch - 1], [0, 2, 4], tol=TOL_BF16 * (layers / 2) ** 0.5, period=period,
+                    stagger=True, sens_report=())
+
+
 @pytest.mark.parametrize("hd,prefix,horizon,batch", [
     (64, 0, 9, 1), (64, 447, 20, 1), (64, 448, 20, 1),     # below and at eight key tiles
     (128, 1000, 64, 1), (256, 255, 16, 2), (256, 530, 50, 1), (32, 2000, 3, 1),
