@@ -117,7 +117,8 @@ struct ravel_model {
   int n_ad = 0;
   void* kva_w = nullptr;  // [n_ad * 2 kvd, w]
   void* oa_all = nullptr;  // [n_ad][w, qd]: the adapters' output projections
-  void* qaT_all = nullptr;  // [n_ad][w, qd]: their query projections transposed (bf16, adapter_fold_ok)
+  std::mutex fold_mu;       // guards the making of qaT_all
+  void* qaT_all = nullptr;  // [n_ad][w, qd]: their query projections transposed, made with the first buffer that folds
   void* fmod_w = nullptr;  // [2w, w]
   float* fmod_b = nullptr;
   void* out_w = nullptr;
@@ -626,6 +627,27 @@ ravel_status enqueue_offset_adapter(ravel_buffer* b, hipStream_t s, KernelRecord
 // 1040 -> 978 (the fold 25); 6 layers, 4 envs 493 -> 486 (the fold 29); 6 layers of 512, one
 // env 232 -> 226; a chunk of 10 Euler steps, 6 layers of 1024, 3228 -> 2917; 5 envs of 512 no gain.
 bool fold_adapters(int B, int H, int n_fop) { return B <= 4 && B * H <= 256 && H >= n_fop; }
+
+// The query projections transposed, for every buffer of this model that folds.
+ravel_status make_fold_weights(ravel_model* m) {
+  std::lock_guard<std::mutex> lk(m->fold_mu);
+  if (m->qaT_all) return RAVEL_OK;
+  const size_t w = m->cfg.width, qd = (size_t)m->cfg.n_q_heads * m->cfg.head_dim, bytes = m->n_ad * w * qd * m->elt;
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess)
+    return fail(RAVEL_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+  hipError_t he = hipSuccess;
+  for (const LayerW& L : m->layers)
+    if (L.adapter >= 0 && he == hipSuccess)
+      he = launch_transpose_bf16((const bf16_t*)L.qa_w, (int)qd, (int)w, (bf16_t*)p + L.adapter * w * qd, 0);
+  if (he == hipSuccess) he = hipDeviceSynchronize();
+  if (he != hipSuccess) {
+    (void)hipFree(p);
+    return fail(RAVEL_E_HIP, std::string("fop.q.w transpose: ") + hipGetErrorString(he));
+  }
+  m->qaT_all = p;
+  return RAVEL_OK;
+}
 
 AdapterArgs adapter_args(const ravel_buffer* b, int ad) {
   const ravel_model* m = b->m;
@@ -1983,7 +2005,6 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
   if (n_ad > 0) {
     ar.want(&m->kva_w, (size_t)n_ad * 2 * kvd * w * E);
     ar.want(&m->oa_all, (size_t)n_ad * w * qd * E);
-    if (m->bf16 && adapter_fold_ok(w, c.n_q_heads, hd, c.n_fop)) ar.want(&m->qaT_all, (size_t)n_ad * w * qd * E);
   }
   if (c.rope_base < 0.f || c.rope_base != c.rope_base) return bail(fail(RAVEL_E_INVALID, "rope_base must be >= 0"));
   if (c.rope_base > 0.f) ar.want((void**)&m->rope_cs, (size_t)H * hd * 4);
@@ -2109,9 +2130,6 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
       UP((p + "fop.gamma").c_str(), Lw.gamma, false);
       UP((p + "fop.q.w").c_str(), Lw.qa_w, true);
       UP((p + "fop.o.w").c_str(), Lw.oa_w, true);
-      if (m->qaT_all && launch_transpose_bf16((const bf16_t*)Lw.qa_w, qd, w,
-                                              (bf16_t*)m->qaT_all + (size_t)Lw.adapter * w * qd, 0) != hipSuccess)
-        return bail(done(fail(RAVEL_E_HIP, p + "fop.q.w transpose")));
       UP((p + "fop.alpha").c_str(), Lw.alpha, false);
       void* dst = (char*)m->kva_w + (size_t)Lw.adapter * 2 * kvd * w * E;
       UP((p + "fop.kv.w").c_str(), dst, true);
@@ -2165,6 +2183,7 @@ ravel_status ravel_create(const ravel_config* cfgp, const ravel_tensor* weights,
 void ravel_destroy(ravel_model* m) {
   if (!m) return;
   if (m->arena) (void)hipFree(m->arena);
+  if (m->qaT_all) (void)hipFree(m->qaT_all);
   delete m;
 }
 
@@ -2227,7 +2246,13 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     ar.want(&b->att, (size_t)BH * qd * E);
     ar.want(&b->qa, (size_t)BH * qd * E);
     if (m->n_ad > 0) ar.want(&b->kva, (size_t)B * c.n_fop * m->n_ad * 2 * kvd * E);
-    if (m->n_ad > 0 && m->qaT_all && fold_adapters(B, H, c.n_fop)) {
+    if (m->n_ad > 0 && m->bf16 && adapter_fold_ok(w, c.n_q_heads, c.head_dim, c.n_fop) &&
+        fold_adapters(B, H, c.n_fop)) {
+      const ravel_status sf = make_fold_weights(m);
+      if (sf != RAVEL_OK) {
+        delete b;
+        return sf;
+      }
       part_elems = std::max(part_elems, (size_t)BH * w);
       const size_t Jp = (size_t)(c.n_q_heads * c.n_fop + 31) / 32 * 32;
       ar.want((void**)&b->akw, (size_t)B * m->n_ad * Jp * w * E);

@@ -86,6 +86,29 @@ def test_adapter_of_tokens_whose_values_cancel(batch):
         assert err <= TOL_BF16
 
 
+def test_a_model_without_folding_buffers_holds_its_weights_once():
+    """The transposed query projections come with the first buffer that folds its adapters
+    and are shared by the next."""
+    import torch
+
+    from paper_2609_34170_amd import ravel
+    s = _shape(layers=8, width=1024, n_q_heads=16, n_kv_heads=1, head_dim=256, mlp_dim=64, prefix_len=0, n_fop=4)
+    wts = synth.draw_weights(s, seed=4)
+    copy = len(s.adapter_layers()) * 16 * 256 * 1024 * 2  # 34 MB; free memory is counted in pages of 2 MB
+
+    def used(make):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        made = make()
+        return made, before - torch.cuda.mem_get_info()[0]
+
+    first = ravel.Model(s, wts)  # (loads the library's kernels)
+    first.close()
+    model, _ = used(lambda: ravel.Model(s, wts))
+    sizes = [used(lambda: ravel.Buffer(model, b, 0)) for b in (5, 1, 1)]
+    assert sizes[1][1] - sizes[2][1] > copy // 2, [n for _, n in sizes]
+
+
 @pytest.mark.parametrize("kw,batch", [
     (dict(action_dim=1, horizon=1), 1),
     (dict(action_dim=16, horizon=16), 1),
