@@ -134,6 +134,11 @@ def test_tiled_gemm_edges(kw, batch):
     _step_velocities(_shape(**kw), batch)
 
 
+@pytest.mark.parametrize("horizon,batch", [(35, 2), (43, 3), (20, 1)])  # 70 and 129 rows; the few-row kernels
+def test_widths_without_the_fused_residual_kernel(horizon, batch):
+    _step_velocities(_shape(layers=1, width=4160, mlp_dim=128, n_fop=0, horizon=horizon), batch)
+
+
 @pytest.mark.parametrize("layers,horizon,batch,period", [
     (8, 25, 6, 3),   # modulation of 25600 columns: tiles of 64 columns
     (9, 25, 6, 3),   # of 28672: the first of tiles of 128 columns; 50 to 75 live rows of 150
