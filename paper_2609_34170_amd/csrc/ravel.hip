@@ -471,8 +471,13 @@ ravel_status run_gemm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const
   if ((K % 8) || (lda % 8) || (ldb % 8)) return fail(RAVEL_E_SHAPE, std::string(name) + ": K and strides must be multiples of 8");
   epi.partial = b->gpart;
   // direct-to-LDS tiles for many rows, and for the layers' GEMMs at any row count (the
-  // few-row kernels stay for the others: at most 64 rows and no chain of partial sums)
-  if ((M > 64 || layer || epi.mode == EPI_PART) && tile_ok(epi)) {
+  // few-row kernels stay for the others: at most 64 rows and no chain of partial sums),
+  // except up to 16 rows of a long K and few columns, where the few-row kernels cut K over
+  // more blocks than there are tiles.  us, tiles / few-row: 16 rows, K = 4608, N = 768 20 / 14,
+  // 3072 23.5 / 17.6, 16384 30 / 55; K = 2048, N = 768 11.2 / 9.9, 3072 12.8 / 11.9; K = 1024,
+  // N = 768 7.8 / 7.5, 3072 8.6 / 9.3; 32 rows, K = 4608, N = 768 20 / 20.
+  const bool narrow = M <= 16 && K >= 2048 && N <= 3072;
+  if ((M > 64 || (layer && !narrow) || epi.mode == EPI_PART) && tile_ok(epi)) {
     const TilePlan t = plan_tile(M, N, K, epi.mode);
     if (epi.mode == EPI_PART && (size_t)t.ksplit * M * N > b->gpart_elems)
       return fail(RAVEL_E_STATE, std::string(name) + ": GEMM workspace too small");

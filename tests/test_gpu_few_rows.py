@@ -139,6 +139,11 @@ def test_widths_without_the_fused_residual_kernel(horizon, batch):
     _step_velocities(_shape(layers=1, width=4160, mlp_dim=128, n_fop=0, horizon=horizon), batch)
 
 
+@pytest.mark.parametrize("horizon,mlp", [(16, 1536), (16, 1552), (17, 1536)])  # the last of the few-row kernels
+def test_few_rows_of_a_long_k(horizon, mlp):
+    _step_velocities(_shape(layers=2, width=2048, mlp_dim=mlp, horizon=horizon, fop_stride=2), 1)
+
+
 @pytest.mark.parametrize("layers,horizon,batch,period", [
     (8, 25, 6, 3),   # modulation of 25600 columns: tiles of 64 columns
     (9, 25, 6, 3),   # of 28672: the first of tiles of 128 columns; 50 to 75 live rows of 150
