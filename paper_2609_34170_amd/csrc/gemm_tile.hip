@@ -29,13 +29,15 @@ bool tile_ok(const GemmArgs& a) {
 // rows), a smaller one fills the chip.  K is split (EPI_PART only: the sums of the ranges
 // are added by the residual kernel that follows) as far as the partial sums stay small
 // against the weights: 8 ranges for up to 128 rows, 4 up to 256 (512 where K >= 4096),
-// 2 up to 2048.  Measured per launch in a chain (us, one CU-filling choice against the
+// 2 up to 2048; K need not divide (4 layers of width 192, 16 rows, K = 6976 = 109 tiles: 236 ->
+// 157 us a step with 8 ranges instead of one).  Measured per launch in a chain (us, one CU-filling choice against the
 // next larger tile), weights from HBM: M = 50, N = 2560, K = 1024 6.0 (32x32) against
 // 7.9 (64x64); M = 200, N = 8192 10.3 (128x64) / 12.9 (128x128, half the CUs); M = 1200
 // 31 (128x128) / 35 (64x64); with the residual kernel M = 200, N = 1024, K = 4096 11.8
 // (64x64, 4 ranges) / 16 (2 ranges); M = 1200 27.7 (2 ranges) / 30 (one).
 TilePlan plan_tile(int M, int N, int K, int mode) {
   const int ks_max = mode != EPI_PART ? 1 : M <= 128 ? 8 : (M <= 256 || (M <= 512 && K >= 4096)) ? 4 : M <= 2048 ? 2 : 1;
+  const auto chunk = [&](int ks) { return (K / 64 + ks - 1) / ks * 64; };
   TilePlan p{};
   for (int t = T128x128; t <= T32x32; ++t) {
     if (t == T32x64 && mode != EPI_GEGLU) continue;  // a gate block and its up block need 32 columns per wave
@@ -48,13 +50,14 @@ TilePlan plan_tile(int M, int N, int K, int mode) {
       return t == T128x128 ? n >= 400 || (n >= kTargetItems && n <= 256) : n >= kTargetItems;
     };
     const int tiles = items_of(t, M, N);
-    while (!enough(tiles * ks) && ks * 2 <= ks_max && K % (ks * 2 * 64) == 0 && K / (ks * 2) >= 256) ks *= 2;
+    // (whole K tiles a range, the last range what is left)
+    while (!enough(tiles * ks) && ks * 2 <= ks_max && K / (ks * 2) >= 256 && (ks * 2 - 1) * chunk(ks * 2) < K) ks *= 2;
     p.tile = t;
     p.ksplit = ks;
     p.items = tiles * ks;
     if (enough(p.items)) break;
   }
-  p.kchunk = K / p.ksplit;
+  p.kchunk = chunk(p.ksplit);
   p.bm = kTiles[p.tile].bm;
   p.bn = kTiles[p.tile].bn;
   return p;
@@ -80,7 +83,7 @@ static hipError_t launch_mode(const GemmArgs& a, const TilePlan& p, hipStream_t 
 }
 
 hipError_t launch_gemm_tile(GemmArgs a, const TilePlan& p, hipStream_t s) {
-  if (!tile_ok(a) || p.kchunk % 64 || p.ksplit * p.kchunk != a.K || (p.ksplit > 1 && a.mode != EPI_PART))
+  if (!tile_ok(a) || p.kchunk % 64 || p.ksplit * p.kchunk < a.K || (p.ksplit - 1) * p.kchunk >= a.K || (p.ksplit > 1 && a.mode != EPI_PART))
     return hipErrorInvalidValue;
   a.ksplit = p.ksplit;
   a.kchunk = p.kchunk;

@@ -128,6 +128,7 @@ def test_output_head_and_update_edges(kw, batch):
     (dict(horizon=64), 1), (dict(horizon=65), 1),      # the few-row kernels end
     (dict(horizon=43), 3), (dict(horizon=52), 5),      # 129 rows (K ranges 8 -> 4), 260 rows (4 -> 2)
     (dict(mlp_dim=80), 2), (dict(mlp_dim=1360), 1),    # hidden rows padded to whole K tiles
+    (dict(mlp_dim=2112), 1), (dict(mlp_dim=6928), 1),  # 33 and 109 K tiles: the last range is shorter
     (dict(width=1040, n_q_heads=4, head_dim=64), 1),   # a last column tile that is nearly empty
 ])
 def test_tiled_gemm_edges(kw, batch):
