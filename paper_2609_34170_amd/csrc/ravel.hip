@@ -1118,6 +1118,7 @@ bool persistent_eligible(const ravel_buffer* b) {
   for (int K : {c.width, qd, c.mlp_dim})
     if (K % 8 || (K + 511) / 512 > kMaxKSplit) return false;
   if (c.width > 4096) return false;  // row sums of squares: at most 64 tiles
+  if (c.offset_mode == RAVEL_OFFSET_MLP && !offset_cond_ok(c.width, c.horizon)) return false;
   if (c.n_fop > attn_keys_per_split_max(hd)) return false;
   const int kmax = attn_keys_per_split_max(hd);
   if ((c.prefix_len + kmax - 1) / kmax + (c.horizon + kmax - 1) / kmax > kMaxAttnSplit) return false;

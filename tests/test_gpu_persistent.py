@@ -136,3 +136,27 @@ def test_fused_prologue_is_bitwise_the_separate_launches(shape_kw, batch, paired
     a_s, X_s = _roll(s, wts, batch, 6, True)
     assert np.array_equal(a_f, a_s)
     assert np.array_equal(X_f, X_s)
+
+
+def test_widths_the_offset_conditioning_does_not_take_do_not_qualify():
+    """The MLP offset form ahead of the persistent kernel takes widths up to 2048: a wider
+    model's buffer refuses the option (its steps would all fail) and steps per operation."""
+    from paper_2609_34170_amd import ravel
+    s = synth.RavelShape(layers=1, width=2112, n_q_heads=2, n_kv_heads=1, head_dim=64, mlp_dim=128, horizon=4,
+                         action_dim=5, prefix_len=9, n_fop=0, fop_obs_dim=16, dtype=W.BF16, batch=1, name="wide")
+    for mode, ok in ((W.OFFSET_MLP, False), (W.OFFSET_CONCAT, True)):
+        s = s.replace(offset_mode=mode)
+        wts = synth.draw_weights(s, seed=4, stress=True)
+        g = GpuRoll(s, wts, 1, seed=0)
+        if ok:
+            g.buf.set_option(ravel.OPT_PERSISTENT, 1)
+        else:
+            with pytest.raises(ravel.RavelError, match="E_STATE"):
+                g.buf.set_option(ravel.OPT_PERSISTENT, 1)
+        assert g.buf.query(ravel.Q_PERSISTENT) == int(ok)
+        o = OracleRavel(s, wts, batch=1, seed=0)
+        k, v = synth.draw_context(s, 0, 0, 0)
+        g.set_context(0, k, v, 0)
+        o.set_context(0, k, v, 0)
+        for st in range(2):
+            assert rel_err(g.step(), o.step(None)) < 2e-2
