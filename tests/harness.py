@@ -82,12 +82,16 @@ class GpuRoll:
 
 
 def run_parity(shape, weights, batch, seed, steps, env_sample=None, fop_mode="tokens",
-               oracle_dtype=np.float64, check_every=10, tol=None, use_graph=True, ctx_seed=0):
-    """Roll both sides `steps` steps; returns (max action error, max state error, n_checked)."""
+               oracle_dtype=np.float64, check_every=10, tol=None, use_graph=True, ctx_seed=0, persistent=None):
+    """Roll both sides `steps` steps; returns (max action error, max state error, n_checked).
+    persistent: True or False selects the execution path (None: the buffer's default)."""
     if tol is None:
         tol = TOL_F32 if shape.dtype == synth.workloads.F32 else TOL_BF16
     envs = list(range(batch)) if env_sample is None else list(env_sample)
     g = GpuRoll(shape, weights, batch, seed, use_graph=use_graph)
+    if persistent is not None:
+        g.buf.set_option(g.rv.OPT_PERSISTENT, 1 if persistent else 0)
+        assert g.buf.query(g.rv.Q_PERSISTENT) == int(persistent)
     o = OracleRavel(shape, weights, batch=len(envs), seed=seed, dtype=oracle_dtype, env_ids=envs)
     o_env = {e: i for i, e in enumerate(envs)}
     sched = synth.context_schedule(shape.replace(batch=batch), steps) if shape.model_kind == 0 else []

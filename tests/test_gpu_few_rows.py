@@ -161,6 +161,7 @@ def test_modulation_of_distinct_conditionings(layers, horizon, batch, period):
 @pytest.mark.parametrize("hd,prefix,horizon,batch", [
     (64, 0, 9, 1), (64, 447, 20, 1), (64, 448, 20, 1),     # below and at eight key tiles
     (128, 1000, 64, 1), (256, 255, 16, 2), (256, 530, 50, 1), (32, 2000, 3, 1),
+    (32, 70, 100, 40), (64, 200, 100, 40),                 # chunks of 128 rows, the last of 72
 ])
 def test_attention_key_ranges(hd, prefix, horizon, batch):
     _step_velocities(_shape(head_dim=hd, prefix_len=prefix, horizon=horizon, layers=1, n_fop=0), batch)
@@ -216,14 +217,17 @@ def test_32_bit_models(kw, batch):
     _step_velocities(_shape(dtype=W.F32, width=128, **kw), batch)
 
 
-@pytest.mark.parametrize("dtype,horizon,batch,S", [
-    (W.BF16, 3, 1, 8),      # more Euler steps than buffer rows: the modulation comes in parts
-    (W.BF16, 20, 4, 5), (W.BF16, 13, 6, 3),
-    (W.F32, 2, 1, 5), (W.F32, 20, 4, 3),
+@pytest.mark.parametrize("dtype,horizon,batch,S,width", [
+    (W.BF16, 3, 1, 8, 256),      # more Euler steps than buffer rows: the modulation comes in parts
+    (W.BF16, 20, 4, 5, 256), (W.BF16, 13, 6, 3, 256),
+    (W.BF16, 70, 1, 72, 256),    # 70 rows at a time (tiles), then 2
+    (W.BF16, 20, 4, 5, 192), (W.BF16, 20, 4, 5, 1152),  # widths whose modulation always takes tiles
+    (W.BF16, 3, 1, 8, 1152), (W.BF16, 70, 1, 72, 192),
+    (W.F32, 2, 1, 5, 256), (W.F32, 20, 4, 3, 256),
 ])
 @pytest.mark.parametrize("offset", [W.OFFSET_MLP, W.OFFSET_CONCAT, W.OFFSET_ADAPTER])
-def test_chunk_modulation_rows(dtype, horizon, batch, S, offset):
-    kw = {**BASE, "dtype": dtype, "horizon": horizon, "offset_mode": offset}
+def test_chunk_modulation_rows(dtype, horizon, batch, S, width, offset):
+    kw = {**BASE, "dtype": dtype, "horizon": horizon, "offset_mode": offset, "width": width}
     _transformer_case("small_bf16", batch, S, np.float64, persistent=None if dtype == W.F32 else False, **kw)
 
 

@@ -27,13 +27,16 @@ def _fixtures():
     return mod
 
 
-def roll_against_fixture(name, use_graph=True):
+def roll_against_fixture(name, use_graph=True, persistent=None):
     fx = _fixtures()
     want = fx.load(name)
     wl, batch, envs, steps, every, _ = fx.FIXTURES[name]
     s = synth.get_config(wl)
     wts = synth.draw_weights(s, seed=fx.WEIGHT_SEED)
     g = GpuRoll(s, wts, batch, fx.RING_SEED, use_graph=use_graph)
+    if persistent is not None:
+        g.buf.set_option(g.rv.OPT_PERSISTENT, 1 if persistent else 0)
+        assert g.buf.query(g.rv.Q_PERSISTENT) == int(persistent)
     sched = synth.context_schedule(s.replace(batch=batch), steps)
     worst_a = worst_x = 0.0
     ck = 0
@@ -57,9 +60,10 @@ def roll_against_fixture(name, use_graph=True):
     return worst_a, worst_x
 
 
-def test_pi_b1_roll_1000_steps():
-    ea, ex = roll_against_fixture("pi_b1_roll1000")
-    print(f"pi_b1 1000 steps: action error {ea:.3e}, ring error {ex:.3e}")
+@pytest.mark.parametrize("persistent", [False, True])
+def test_pi_b1_roll_1000_steps(persistent):
+    ea, ex = roll_against_fixture("pi_b1_roll1000", persistent=persistent)
+    print(f"pi_b1 1000 steps persistent={persistent}: action error {ea:.3e}, ring error {ex:.3e}")
 
 
 def test_large_b16_all_24_layers():

@@ -26,12 +26,11 @@ def test_tiny_fp32_adapter_roll_matches_oracle():
 
 
 @pytest.mark.parametrize("persistent", [True, False])
-def test_small_bf16_adapter_roll_matches_oracle_on_both_paths(persistent, monkeypatch):
-    if not persistent:
-        monkeypatch.setenv("RAVEL_NO_PERSISTENT", "1")
+def test_small_bf16_adapter_roll_matches_oracle_on_both_paths(persistent):
     s = synth.get_config("small_bf16").replace(layers=2, offset_mode=W.OFFSET_ADAPTER, context_period=4)
     wts = synth.draw_weights(s, seed=22, stress=True)
-    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8)
+    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8,
+                           persistent=persistent)
     print(f"small_bf16 adapter persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 
@@ -45,14 +44,16 @@ def test_staggered_refreshes_give_each_env_its_own_offset():
     print(f"small_bf16 adapter B=5 staggered: action err {ea:.2e}, state err {ex:.2e}")
 
 
-def test_pi_width_adapter_roll_on_the_persistent_path():
+@pytest.mark.parametrize("persistent", [True, False])
+def test_pi_width_adapter_roll_on_both_paths(persistent):
     """The pi-style widths (w = 1024, 256-dim heads, 50 slots) with two layers: the
     action-time MLP's 2112-wide inputs and the 256-wide adapter bottleneck through the
-    few-row GEMMs ahead of the persistent kernel."""
+    few-row GEMMs ahead of the persistent kernel, and of a kernel per operation."""
     s = synth.get_config("pi_b1").replace(layers=2, offset_mode=W.OFFSET_ADAPTER, context_period=2)
     wts = synth.draw_weights(s, seed=24, stress=True)
-    ea, ex, n = run_parity(s, wts, batch=1, seed=8, steps=6, oracle_dtype=np.float32, check_every=3)
-    print(f"pi widths adapter: action err {ea:.2e}, state err {ex:.2e}")
+    ea, ex, n = run_parity(s, wts, batch=1, seed=8, steps=6, oracle_dtype=np.float32, check_every=3,
+                           persistent=persistent)
+    print(f"pi widths adapter persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 
 @pytest.mark.parametrize("persistent", [False, True])
@@ -78,16 +79,16 @@ def test_training_loss_with_the_adapter_form():
 
 def test_ragged_shapes_with_the_adapter_form_and_rotary_positions():
     """63 rows (3 envs x 21 slots), 77 prefix tokens, 32-dim heads, width 256 (adapter
-    bottleneck 64): the adapter form on the persistent path, then with rotary positions
-    on the per-kernel path."""
+    bottleneck 64): the adapter form, then with rotary positions, on both paths."""
     base = dict(layers=2, width=256, n_q_heads=4, n_kv_heads=2, head_dim=32, mlp_dim=512, horizon=21,
                 action_dim=5, prefix_len=77, n_fop=3, fop_obs_dim=16, dtype=W.BF16, batch=3,
                 offset_mode=W.OFFSET_ADAPTER, context_period=3, stagger=True, delta_bias=0.1, name="ragged_ada")
-    for rope in (0.0, 1000.0):
+    for rope, persistent in ((0.0, True), (0.0, False), (1000.0, True), (1000.0, False)):
         s = synth.RavelShape(rope_base=rope, **base)
         wts = synth.draw_weights(s, seed=25, stress=True)
-        ea, ex, n = run_parity(s, wts, batch=3, seed=9, steps=9, oracle_dtype=np.float64, check_every=3)
-        print(f"ragged adapter rope={rope}: action err {ea:.2e}, state err {ex:.2e}")
+        ea, ex, n = run_parity(s, wts, batch=3, seed=9, steps=9, oracle_dtype=np.float64, check_every=3,
+                               persistent=persistent)
+        print(f"ragged adapter rope={rope} persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 
 def test_batch64_widths_with_the_adapter_form_sampled_envs():

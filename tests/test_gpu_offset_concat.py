@@ -24,12 +24,11 @@ def test_tiny_fp32_concat_roll_matches_oracle():
 
 
 @pytest.mark.parametrize("persistent", [True, False])
-def test_small_bf16_concat_roll_matches_oracle_on_both_paths(persistent, monkeypatch):
-    if not persistent:
-        monkeypatch.setenv("RAVEL_NO_PERSISTENT", "1")
+def test_small_bf16_concat_roll_matches_oracle_on_both_paths(persistent):
     s = synth.get_config("small_bf16").replace(layers=2, offset_mode=W.OFFSET_CONCAT, context_period=4)
     wts = synth.draw_weights(s, seed=12, stress=True)
-    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8)
+    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8,
+                           persistent=persistent)
     print(f"small_bf16 concat persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 

@@ -22,22 +22,23 @@ def test_tiny_fp32_rope_roll_matches_oracle():
 
 
 @pytest.mark.parametrize("persistent", [True, False])
-def test_small_bf16_rope_roll_matches_oracle_on_both_paths(persistent, monkeypatch):
-    if not persistent:
-        monkeypatch.setenv("RAVEL_NO_PERSISTENT", "1")
+def test_small_bf16_rope_roll_matches_oracle_on_both_paths(persistent):
     s = synth.get_config("small_bf16").replace(layers=2, rope_base=100.0, context_period=4)
     wts = synth.draw_weights(s, seed=32, stress=True)
-    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8)
+    ea, ex, n = run_parity(s, wts, batch=2, seed=6, steps=24, oracle_dtype=np.float64, check_every=8,
+                           persistent=persistent)
     print(f"small_bf16 rope persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 
-def test_pi_widths_rope_roll_matches_oracle():
+@pytest.mark.parametrize("persistent", [True, False])
+def test_pi_widths_rope_roll_matches_oracle(persistent):
     """256-dim heads, 816 prefix tokens (positions up to 865), one env: the persistent
-    kernel with its rotary phase after every QKV projection."""
+    kernel with its rotary phase after every QKV projection, and a kernel per operation."""
     s = synth.get_config("pi_b1").replace(layers=2, rope_base=10000.0, context_period=2)
     wts = synth.draw_weights(s, seed=33, stress=True)
-    ea, ex, n = run_parity(s, wts, batch=1, seed=8, steps=6, oracle_dtype=np.float32, check_every=3)
-    print(f"pi widths rope: action err {ea:.2e}, state err {ex:.2e}")
+    ea, ex, n = run_parity(s, wts, batch=1, seed=8, steps=6, oracle_dtype=np.float32, check_every=3,
+                           persistent=persistent)
+    print(f"pi widths rope persistent={persistent}: action err {ea:.2e}, state err {ex:.2e}")
 
 
 def test_persistent_kernel_has_a_rotary_phase():

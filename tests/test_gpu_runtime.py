@@ -86,6 +86,18 @@ def test_graph_follows_the_execution_path_switch():
     assert rel_err(np.stack(outs_g), np.stack(outs_o)) < 2e-2
 
 
+@pytest.mark.parametrize("layers,width,persistent", [(3, 512, 1), (4, 512, 0), (3, 576, 0)])
+def test_default_execution_path(layers, width, persistent, monkeypatch):
+    """The persistent kernel up to 3 layers of width 512, unless the environment declines it."""
+    from paper_2609_34170_amd import ravel
+    s, _ = _tiny_bf16()
+    s = s.replace(layers=layers, width=width)
+    wts = synth.draw_weights(s, seed=4)
+    assert GpuRoll(s, wts, 2, seed=0).buf.query(ravel.Q_PERSISTENT) == persistent
+    monkeypatch.setenv("RAVEL_NO_PERSISTENT", "1")
+    assert GpuRoll(s, wts, 2, seed=0).buf.query(ravel.Q_PERSISTENT) == 0
+
+
 # ---------------------------------------------------------------------------
 # a failed launch of the layers' kernel
 # ---------------------------------------------------------------------------
