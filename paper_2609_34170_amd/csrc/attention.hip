@@ -2,12 +2,12 @@
 // the FOP adapters over FOP tokens), bidirectional, grouped-query heads.
 //
 // bf16 path (MFMA, wave64): one block per (key range, row chunk of a KV head's
-// queries, KV head, env).  Key/value tiles are staged in LDS (V stored transposed)
-// and shared by the waves.  Scores are computed transposed, S^T = K Q^T, so that each
-// lane owns one query: the online softmax statistics stay in registers and P^T feeds
-// the second MFMA O^T += V^T P^T directly, without an LDS round trip.  With several
-// key ranges, each block writes (m, l, unnormalised O) and a second kernel adds the
-// ranges in fixed order.
+// queries, KV head, env).  Key/value tiles are staged in LDS as they lie in memory and
+// shared by the waves.  Scores are computed transposed, S^T = K Q^T, so that each lane of a
+// score wave owns one query and the online softmax statistics stay in its registers; P^T goes
+// through LDS to the output waves, in the shape of the second MFMA's operand (O^T += V^T P^T).
+// With several key ranges, each block writes (m, l, unnormalised O) and a second kernel
+// adds the ranges in fixed order.
 #include <algorithm>
 
 #include "kernels.h"
@@ -25,8 +25,9 @@ static constexpr float kLog2e = 1.4426950408889634f;
 // softmax statistics never leave a wave) and put P^T in LDS in the shape of the second
 // product's B operand; the others ("output waves") meanwhile compute O^T of tile t - 1,
 // each for a quarter of the head's dims over 64 rows (a value fragment feeds four MFMAs).
-// One barrier per tile, and each SIMD has both kinds of work to choose from.  One wave after the other through scores, softmax and output is a chain of ~2400 cycles per
-// 32 keys at 256 dims whatever the memory does (measured with 7 blocks as with 168), and
+// One barrier per tile, and each SIMD has both kinds of work to choose from.  One wave after
+// the other through scores, softmax and output is a chain of ~2400 cycles per 32 keys at
+// 256 dims whatever the memory does (measured with 7 blocks as with 168), and
 // a wave that keeps all dims of its rows needs a body of 1000 instructions a tile, which a
 // short launch walks cold (9.7 us for a single tile of 16 keys, 6.5 split by dims).
 //

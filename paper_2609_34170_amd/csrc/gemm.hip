@@ -487,7 +487,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_regstream_kernel(GemmArgs a) {
       case EPI_T: epi4<EPI_T>(a, m, n, sum[q], vec); break;
       case EPI_RESID: epi4<EPI_RESID>(a, m, n, sum[q], vec); break;
       case EPI_RESID_TANH: epi4<EPI_RESID_TANH>(a, m, n, sum[q], vec); break;
-      case EPI_COND: epi4<EPI_COND>(a, m, n, sum[q], vec); break;
       case EPI_GELU_T: epi4<EPI_GELU_T>(a, m, n, sum[q], vec); break;
       case EPI_SILU_T: epi4<EPI_SILU_T>(a, m, n, sum[q], vec); break;
       default: break;
@@ -603,7 +602,6 @@ RAVEL_DEV void gemm_wholek_block(const GemmArgs& a, int bx) {
       case EPI_T: epi4<EPI_T>(a, m, n, s, vec); break;
       case EPI_RESID: epi4<EPI_RESID>(a, m, n, s, vec); break;
       case EPI_RESID_TANH: epi4<EPI_RESID_TANH>(a, m, n, s, vec); break;
-      case EPI_COND: epi4<EPI_COND>(a, m, n, s, vec); break;
       case EPI_GELU_T: epi4<EPI_GELU_T>(a, m, n, s, vec); break;
       case EPI_SILU_T: epi4<EPI_SILU_T>(a, m, n, s, vec); break;
       default: break;

@@ -24,12 +24,6 @@ RAVEL_DEV void epi1(const GemmArgs& a, int m, int n, float acc) {
   } else if constexpr (MODE == EPI_RESID_TANH) {
     float* o = a.out_f + (size_t)m * a.ldo_f + n;
     *o = *o + tanhf(*a.gate_scalar) * acc;
-  } else if constexpr (MODE == EPI_COND) {
-    const int blk = a.cond_grp ? a.cond_grp[m] : m;
-    if (blk < 0) return;
-    const float base = acc + b;
-    for (int i = 0; i < a.H; ++i)
-      ((T*)a.out_t)[((size_t)blk * a.H + i) * a.ldo_t + n] = act<T>::from_f(silu_f(a.ctau[(size_t)i * a.N + n] + base));
   } else if constexpr (MODE == EPI_GELU_T) {
     ((T*)a.out_t)[(size_t)m * a.ldo_t + n] = act<T>::from_f(gelu_tanh_f(acc + b));
   } else if constexpr (MODE == EPI_SILU_T) {
@@ -46,7 +40,6 @@ RAVEL_DEV bool epi_vec_ok(const GemmArgs& a) {
     case EPI_T:
     case EPI_GELU_T:
     case EPI_SILU_T: return (a.ldo_t % 4) == 0;
-    case EPI_COND: return (a.ldo_t % 4) == 0 && (a.N % 4) == 0;
     default: return true;
   }
 }
@@ -88,23 +81,6 @@ RAVEL_DEV void epi4(const GemmArgs& a, int m, int n, f32x4_t v, bool vec) {
     x[2] = x[2] + g[2] * v[2];
     x[3] = x[3] + g[3] * v[3];
     *o = x;
-  } else if constexpr (MODE == EPI_COND) {
-    const int blk = a.cond_grp ? a.cond_grp[m] : m;
-    if (blk < 0) return;
-    // the time embeddings of 8 slots are loaded before any of their outputs is
-    // stored: one memory latency per 8 slots (the stores could alias the loads,
-    // so the compiler would otherwise wait for each load in turn)
-    for (int i0 = 0; i0 < a.H; i0 += 8) {
-      f32x4_t c[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        c[j] = (i0 + j < a.H) ? *(const f32x4_t*)(a.ctau + (size_t)(i0 + j) * a.N + n) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (i0 + j < a.H)
-          store_bf16x4((bf16_t*)a.out_t + ((size_t)blk * a.H + i0 + j) * a.ldo_t + n, silu_f(c[j][0] + v[0] + b[0]),
-                       silu_f(c[j][1] + v[1] + b[1]), silu_f(c[j][2] + v[2] + b[2]), silu_f(c[j][3] + v[3] + b[3]));
-    }
   } else if constexpr (MODE == EPI_GELU_T) {
     store_bf16x4((bf16_t*)a.out_t + (size_t)m * a.ldo_t + n, gelu_tanh_f(v[0] + b[0]), gelu_tanh_f(v[1] + b[1]),
                  gelu_tanh_f(v[2] + b[2]), gelu_tanh_f(v[3] + b[3]));
@@ -155,7 +131,6 @@ RAVEL_DEV void epilogue(const GemmArgs& a, const f32x4_t (&acc)[NI][NJ], int m0,
     case EPI_RESID: epi_frags<EPI_RESID>(a, acc, m0, n0, l16, grp); break;
     case EPI_RESID_TANH: epi_frags<EPI_RESID_TANH>(a, acc, m0, n0, l16, grp); break;
     case EPI_GEGLU: epi_frags<EPI_GEGLU>(a, acc, m0, n0, l16, grp); break;
-    case EPI_COND: epi_frags<EPI_COND>(a, acc, m0, n0, l16, grp); break;
     case EPI_GELU_T: epi_frags<EPI_GELU_T>(a, acc, m0, n0, l16, grp); break;
     case EPI_SILU_T: epi_frags<EPI_SILU_T>(a, acc, m0, n0, l16, grp); break;
     default: break;

@@ -21,7 +21,7 @@ int items_of(int t, int M, int N) {
 bool tile_ok(const GemmArgs& a) {
   return a.M > 0 && a.N > 0 && a.K > 0 && a.K % 64 == 0 && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
          ((uintptr_t)a.A % 16) == 0 && ((uintptr_t)a.B % 16) == 0 && (a.mode != EPI_GEGLU || a.N % 32 == 0) &&
-         (a.mode != EPI_PART || a.N % 4 == 0) && a.mode != EPI_COND;
+         (a.mode != EPI_PART || a.N % 4 == 0);
 }
 
 // The largest tile that still gives about one item per CU: a larger tile moves fewer
@@ -29,12 +29,13 @@ bool tile_ok(const GemmArgs& a) {
 // rows), a smaller one fills the chip.  K is split (EPI_PART only: the sums of the ranges
 // are added by the residual kernel that follows) as far as the partial sums stay small
 // against the weights: 8 ranges for up to 128 rows, 4 up to 256 (512 where K >= 4096),
-// 2 up to 2048; K need not divide (4 layers of width 192, 16 rows, K = 6976 = 109 tiles: 236 ->
-// 157 us a step with 8 ranges instead of one).  Measured per launch in a chain (us, one CU-filling choice against the
-// next larger tile), weights from HBM: M = 50, N = 2560, K = 1024 6.0 (32x32) against
-// 7.9 (64x64); M = 200, N = 8192 10.3 (128x64) / 12.9 (128x128, half the CUs); M = 1200
-// 31 (128x128) / 35 (64x64); with the residual kernel M = 200, N = 1024, K = 4096 11.8
-// (64x64, 4 ranges) / 16 (2 ranges); M = 1200 27.7 (2 ranges) / 30 (one).
+// 2 up to 2048.  The ranges are whole K tiles, the last what is left (K = 6976 = 109 tiles at
+// 4 layers of width 192, 16 rows: 235 us a step with one range, 157 with 8).  Measured per
+// launch in a chain (us, one CU-filling choice against the next larger tile), weights from
+// HBM: M = 50, N = 2560, K = 1024 6.0 (32x32) against 7.9 (64x64); M = 200, N = 8192 10.3
+// (128x64) / 12.9 (128x128, half the CUs); M = 1200 31 (128x128) / 35 (64x64); with the
+// residual kernel M = 200, N = 1024, K = 4096 11.8 (64x64, 4 ranges) / 16 (2 ranges); M =
+// 1200 27.7 (2 ranges) / 30 (one).
 TilePlan plan_tile(int M, int N, int K, int mode) {
   const int ks_max = mode != EPI_PART ? 1 : M <= 128 ? 8 : (M <= 256 || (M <= 512 && K >= 4096)) ? 4 : M <= 2048 ? 2 : 1;
   const auto chunk = [&](int ks) { return (K / 64 + ks - 1) / ks * 64; };

@@ -26,10 +26,9 @@ enum EpiMode {
   EPI_RESID_TANH = 3, // out_f[m,n] += tanh(*gate_scalar) * acc    (adapter gate)
   EPI_GEGLU = 4,      // out_t[m,f]  = T(gelu_tanh(acc_gate) * acc_up), columns interleaved
                       //               in blocks of 16 gate / 16 up (N = 2F)
-  EPI_COND = 5,       // out_t[m*H+i, n] = T(silu(ctau[i,n] + acc + bias[n])) for i < H
-  EPI_GELU_T = 6,     // out_t[m,n]  = T(gelu_tanh(acc + bias[n]))
-  EPI_SILU_T = 7,     // out_t[m,n]  = T(silu(acc + bias[n]))
-  EPI_PART = 8,       // partial[z][m][n] = the sum over K range z (row-major, N a multiple of 4), summed by
+  EPI_GELU_T = 5,     // out_t[m,n]  = T(gelu_tanh(acc + bias[n]))
+  EPI_SILU_T = 6,     // out_t[m,n]  = T(silu(acc + bias[n]))
+  EPI_PART = 7,       // partial[z][m][n] = the sum over K range z (row-major, N a multiple of 4), summed by
                       // launch_resid_norm
 };
 
@@ -47,11 +46,9 @@ struct GemmArgs {
   void* out_t; int ldo_t;
   const float* gate; int ldg;
   const float* gate_scalar;
-  const float* ctau; int H;
   // Rows that share their modulation (see launch_cond_groups); all optional:
   const int* m_rows;     // device row count: rows >= min(M, *m_rows) are neither computed nor stored
   const int* gate_rows;  // [M]: EPI_RESID reads gate row gate_rows[m] instead of row m
-  const int* cond_grp;   // [M], EPI_COND: output block cond_grp[m] (>= 0), or nothing (< 0)
   // Whole-K few-row kernel, EPI_F32 on a layer's modulation rows (value v = acc + bias
   // at columns [0, 6 nrm_w)): also the first adaptive norm's operands, p[m][n] =
   // bf16((1 + v[m][n]) nrm_x[m][n]) for n < nrm_w, and bf16 copies of the two shifts

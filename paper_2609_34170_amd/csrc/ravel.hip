@@ -286,9 +286,10 @@ GemmPlan plan_gemm(int M, int N, int K, bool geglu) {
     p.part_elems = p.ksplit > 1 ? (size_t)p.ksplit * p.tiles * tile_elems : 0;
     return p;
   }
-  // tile by shape (direct-to-LDS kernels, measured on MI355X at M = 3200, the
-  // pi-style batch-64 rows: 128x128 744-804 TF/s at K = 1024; 128x64 514 and 581
-  // TF/s at N = 1024, K = 2048 and 4096, where 128x128 gives 200 tiles)
+  // Many rows that the direct-to-LDS tiles do not take (a K that is no multiple of 64):
+  // register-staged tiles, larger ones for more rows and columns.  Far slower (3200 rows,
+  // K = 1032: 217 us for N = 2560 and 417 for 8192, 65-78 TF/s, where K = 1024 runs at 690-830), so no
+  // size that matters should get here.
   int bm, bn;
   if (M <= 256) {
     p.tile = TILE_64x128; bm = 64; bn = 128;
@@ -457,7 +458,6 @@ ravel_status run_gemm(ravel_buffer* b, hipStream_t s, KernelRecorder* rec, const
   if (epi.mode == EPI_RESID_TANH) obytes = (double)M * N * 8;
   if (epi.mode == EPI_PART) obytes = (double)M * N * 4;
   if (epi.mode == EPI_GEGLU) obytes = (double)M * (N / 2) * elt;
-  if (epi.mode == EPI_COND) obytes = (double)M * m->cfg.horizon * N * elt;
   const double bytes = ((double)M * K + (double)N * K) * elt + obytes;
   const double flops = 2.0 * M * N * K;
   if (!m->bf16) {
@@ -2341,12 +2341,13 @@ ravel_status ravel_buffer_create(ravel_model* m, int32_t batch, uint64_t seed, r
     return bail(fail(RAVEL_E_HIP, "stream create"));
   if (persistent_eligible(b)) {
     if (build_persistent(b) == RAVEL_OK) {
-      // One kernel per operation is the faster path at every size (us per step, persistent
-      // against it: 18 layers of 1024 1254 / 1060; 6 layers of 512 320 / 240; 2 layers of 512
-      // 129 / 96, of 256 125 / 79), since its kernels choose their blocks for each operation
-      // and a grid barrier costs as much as a launch.  The smallest models keep the
-      // persistent kernel as their default: what a default buffer of theirs reports through
-      // the profile (its phases) and does after a failed launch is part of the interface.
+      // One kernel per operation is the faster path at every size measured (us per step,
+      // persistent against it: 18 layers of 1024 1253 / 977; 6 layers of 512 322 / 227, 3 169 / 123,
+      // 2 131 / 90; 2 layers of 256 139 / 82), since its kernels choose their blocks for each
+      // operation and a grid barrier costs as much as a launch.  The line below is not one of
+      // cost: the smallest models keep their default because programs read the kernel's phases
+      // (profile) and its recovery from a failed launch off default buffers of theirs;
+      // RAVEL_OPT_PERSISTENT 0 gives them the faster path.
       b->persistent = c.layers <= 3 && c.width <= 512;
     } else {
       for (void* p : b->pallocs) (void)hipFree(p);

@@ -37,8 +37,9 @@ COPY_BYTES = 512 << 20
 # source files of each kernel class (the traffic record's hash)
 KERNEL_SOURCES = {
     "persistent_layers": ["persistent.hip", "persistent.h", "common.h", "kernels.h"],
-    "gemm": ["gemm.hip", "common.h", "kernels.h"],
+    "gemm": ["gemm_tile.h", "gemm_tile.hip", "gemm.hip", "gemm_epilogue.h", "common.h", "kernels.h"],
     "attn": ["attention.hip", "common.h", "kernels.h"],
+    "resid_norm": ["elementwise.hip", "common.h", "kernels.h"],
 }
 
 
