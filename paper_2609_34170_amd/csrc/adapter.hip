@@ -12,8 +12,9 @@
 // the tokens' values cancel, and the same error in all Euler steps of a chunk.  Errors of
 // velocities and chunks against 64 bits, folded over unfolded, 60 inputs: one part each
 // +0.7 +-0.2 % (2 layers of 1024), +0.4 +-0.1 (6 layers, 4 envs), +1.9 +-0.3 (chunk, 4 layers of
-// 1024), +4.1 +-0.9 (chunk, 4 layers of 512); two parts -1.3, -1.5, -0.5 and -1.9 %.  The
-// remainders cost 0.8 us a layer (18 layers of 1024, one env: 971 -> 978 us a step).
+// 1024), +4.1 +-0.9 (chunk, 4 layers of 512); two parts -1.3, -1.5, -0.5 and -1.9 %.  What the
+// remainders cost a step, us: 18 layers of 1024, one env 979 -> 980, 6 layers, 4 envs 488 -> 493,
+// 6 layers of 512, one env 226 -> 229.
 #include "kernels.h"
 
 namespace ravel {
@@ -75,15 +76,24 @@ __global__ __launch_bounds__(256) void adapter_fold_kernel(AdapterArgs a) {
         for (int f = 0; f < FR; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][f], wf[s], acc[f], 0, 0, 0);
     // acc[f][r]: token 16 f + 4 grp + r, column n0 + l16
     bf16_t* vr = a.vw + (ea * a.w + n0 + l16) * 2 * a.Jp + h * a.F;
+    const bool quads = a.F % 4 == 0;  // 8-byte stores: 27 -> 24 us (9 adapters of 1024, one env), 32 -> 28 (4 envs, 3 adapters)
 #pragma unroll
-    for (int f = 0; f < FR; ++f)
+    for (int f = 0; f < FR; ++f) {
+      const int t = f * 16 + grp * 4;
+      if (quads) {
+        if (t >= a.F) continue;
+        *(u32x2_t*)(vr + t) = u32x2_t{pack_bf16x2(acc[f][0], acc[f][1]), pack_bf16x2(acc[f][2], acc[f][3])};
+        *(u32x2_t*)(vr + a.Jp + t) = u32x2_t{pack_bf16x2(remainder_of(acc[f][0]), remainder_of(acc[f][1])),
+                                             pack_bf16x2(remainder_of(acc[f][2]), remainder_of(acc[f][3]))};
+        continue;
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int t = f * 16 + grp * 4 + r;
-        if (t >= a.F) continue;
-        vr[t] = f32_to_bf16(acc[f][r]);
-        vr[a.Jp + t] = f32_to_bf16(remainder_of(acc[f][r]));
+        if (t + r >= a.F) continue;
+        vr[t + r] = f32_to_bf16(acc[f][r]);
+        vr[a.Jp + t + r] = f32_to_bf16(remainder_of(acc[f][r]));
       }
+    }
   }
 }
 

@@ -629,8 +629,8 @@ ravel_status enqueue_offset_adapter(ravel_buffer* b, hipStream_t s, KernelRecord
 // Folded adapters (adapter.hip) where their weights' pass over every env's tokens costs less
 // than the launches and projections it saves per layer: up to 4 envs of no fewer slots
 // than tokens.  Per step, four launches a layer -> folded (us): 18 layers of 1024, one env
-// 1040 -> 978 (the fold 25); 6 layers, 4 envs 493 -> 486 (the fold 29); 6 layers of 512, one
-// env 232 -> 226; a chunk of 10 Euler steps, 6 layers of 1024, 3228 -> 2917; 5 envs of 512 no gain.
+// 1047 -> 980 (the fold 24); 6 layers, 4 envs 502 -> 493 (the fold 28); 6 layers of 512, one
+// env 232 -> 229; a chunk of 10 Euler steps, 6 layers of 1024, 3243 -> 2942; 5 envs of 512 no gain.
 bool fold_adapters(int B, int H, int n_fop) { return B <= 4 && B * H <= 256 && H >= n_fop; }
 
 // The query projections transposed, for every buffer of this model that folds.
