@@ -193,7 +193,8 @@ void ravel_buffer_destroy(ravel_buffer* buf);
  *                           the step's kernels eagerly.
  *   RAVEL_OPT_DEBUG         1: synchronise and check for NaN/Inf after each kernel.
  *   RAVEL_OPT_PERSISTENT    1 (available for a bf16 model whose B*H rows fit one 64-row
- *                           tile; the default up to 3 layers of width 512): run the
+ *                           tile, of width up to 2048 with the MLP offset form and 4096
+ *                           otherwise; the default up to 3 layers of width 512): run the
  *                           transformer layers as a single persistent kernel (one
  *                           block per CU, grid barriers between phases) between the
  *                           few kernels around it; 0: one kernel per operation.
