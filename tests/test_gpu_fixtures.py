@@ -1,6 +1,6 @@
 """The two long parity rolls compared with oracle outputs stored by
 tests/golden/make_oracle_fixtures.py (oracle only, same seeded inputs): the pi-style
-expert at batch 1 rolled 1000 steps (the benchmark spec's roll length for that workload), and
+expert at batch 1 rolled 1000 steps (that workload's roll length), and
 the large expert at all 24 of its layers at batch 16 (envs 0 and 15) across a
 context refresh.  Every released action and the ring at the stored checkpoints are
 compared at max normwise relative error 2e-2 (bf16 with fp32 accumulation)."""
